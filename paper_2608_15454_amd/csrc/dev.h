@@ -274,5 +274,19 @@ __device__ __forceinline__ float multi_sum(float (&v)[V]) {
   return group_sum<64 / V>(v[0]);  // the 64 / V lanes holding the same value
 }
 
+// 1 KB from global memory to LDS: lane l's 16 bytes at sbase + voff go to m0 + 16 l.  The
+// load has no register result; its arrival is counted by vmcnt, which the kernel waits
+// for itself (a load the compiler knows of makes it wait for every load in flight before
+// any LDS read).
+__device__ __forceinline__ void dma16(uint32_t m0, uint32_t voff, const char* sbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff), "s"(sbase)
+               : "memory");
+}
+
+// LDS byte address of p, for dma16.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
 }  // namespace dev
 }  // namespace mbp

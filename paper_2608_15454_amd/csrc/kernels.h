@@ -88,6 +88,7 @@ struct Attn {
   float scale;
   float* O;  // [M, ldo]
   int32_t ldo;
+  int32_t split;  // write O's rows as split rows (PlaneLinear) instead of float32
 };
 
 // Optional events stamped by the first kernel's start and the last kernel's end of
@@ -100,6 +101,37 @@ struct Ev {
 // Launchers.  wdt: 0 = float32 weights, 1 = bfloat16.  kvt: cache element type,
 // 0 = float32, 1 = bfloat16, 2 = float16.
 hipError_t launch_linear(const Linear& L, int wdt, float* inv_rms_scratch, hipStream_t st, const Ev& ev = Ev());
+// A linear layer on split rows: a row of K values as K / 32 groups of 64 bfloat16, the
+// group's 32 hi = bf16(x), then its 32 lo = bf16(x - hi) (4 K bytes, as in float32).  x
+// holds M such rows of ldx values (RMSNorm and gain already applied).  epi as Linear's,
+// except that SWIGLU writes split rows of ldy values to y.
+struct PlaneLinear {
+  const uint16_t* x;
+  int32_t ldx, M, K, N;
+  Mats mats;
+  int32_t kind;
+  Epi epi;
+  uint16_t* y;
+  int32_t ldy;
+  float* part;  // split-K scratch (kGemmPartFloats floats)
+};
+// Whether a linear of this shape (bfloat16 weights) runs on split rows; n_mat: rows of
+// one matrix of a fused weight (N otherwise).
+bool planes_fit(int M, int N, int K, int n_mat);
+hipError_t launch_planes(const PlaneLinear& P, hipStream_t st, const Ev& ev = Ev());
+// Tile (128 or 256) and K splits launch_planes takes for a shape, and the launch at a
+// given choice.
+struct PlanesPlan {
+  int tile, ks;
+};
+PlanesPlan planes_plan(const PlaneLinear& P);
+hipError_t launch_planes_at(const PlaneLinear& P, PlanesPlan plan, hipStream_t st, const Ev& ev = Ev());
+// The sums of ks partial products in L.part and the epilogue (the second half of a
+// split-K launch: only ev.stop is stamped).
+hipError_t launch_gemm_finish(const Linear& L, int ks, hipStream_t st, const Ev& ev);
+// Split rows of M rows of d floats: x, or RMSNorm(x) * gain when gain is set.
+hipError_t launch_split_rows(const float* x, const float* gain, float eps, uint16_t* y, int d, int M, hipStream_t st,
+                             const Ev& ev = Ev());
 // Whether launch_linear takes the weight-streaming GEMV path for L.
 bool linear_is_gemv(const Linear& L, int wdt);
 // Split-KV attention (blocks of four waves over 256-key splits) followed by a merge

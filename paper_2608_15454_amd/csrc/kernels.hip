@@ -8,7 +8,7 @@
 //   K >= 2048; 64 of float32): each weight byte is read from HBM once per launch with
 //   16-byte loads, issued before the activations are loaded;
 // - for more rows of bfloat16 weights, the row GEMM (17..64 rows) and MFMA tiles of
-//   64 x 64 (split-K), 128 x 128 and 256 x 256.
+//   64 x 64 (split-K); passes of 65 rows and more run on split rows (planes.hip).
 // Decode attention splits the keys over blocks and merges the splits in a second
 // kernel; several rows of one sequence share each K/V tile (the multi-query kernel).
 // Prefill and the full-sequence forward use MFMA attention over 64-query tiles.
@@ -68,6 +68,19 @@ __device__ __forceinline__ void epi_pair(const Epi& e, int i, int n, float a0, f
   if (e.kvt == 2) cache_store2<_Float16>(cache, off, a0, a1);
   else if (e.kvt == 1) cache_store2<uint16_t>(cache, off, a0, a1);
   else cache_store2<float>(cache, off, a0, a1);
+}
+
+// Element (i, c) of an attention output: float32, or hi / lo halves of a split row.
+__device__ __forceinline__ void store_o(float* O, int ldo, int split, int i, int c, float v) {
+  if (!split) {
+    O[(size_t)i * ldo + c] = v;
+    return;
+  }
+  uint32_t hi, lo;
+  bf16_hi_lo2(v, 0.f, hi, lo);
+  uint16_t* o = reinterpret_cast<uint16_t*>(O) + (size_t)i * 2 * ldo + 2 * (c & ~31) + (c & 31);
+  o[0] = (uint16_t)hi;
+  o[32] = (uint16_t)lo;
 }
 
 // Launch with optional start/stop events stamped by the kernel's own execution.
@@ -593,272 +606,6 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(Linear L) {
   }
 }
 
-// The same product for large M (prefill, long commits, the full-sequence forward):
-// one output tile of BM x BN per block of WM x WN waves, each wave TI x TJ blocks of
-// v_mfma_f32_32x32x16_bf16 (X in bfloat16 hi + lo as above), K in steps of 32.  Two
-// LDS stages and two register stages: the X and weight rows of step k+2 are requested
-// while step k's MFMAs run and step k+1 is staged, so each fetch has two steps to
-// arrive (the steps are latency-bound otherwise); one barrier per step.  The 256 x 256
-// tile stages step k+1 before step k's MFMAs in program order, the 128 x 128 tile after
-// them (each order measured faster on its tile).  Every thread
-// stages four 4-wide pieces of X rows and two 8-wide pieces of weight rows per step
-// (BM = BN = threads / 2).
-// Two shapes: 128 x 128 (four waves of 64 x 64, two blocks per CU) and 256 x 256 (eight
-// waves of 64 rows x 128 columns, one block per CU), which stages half the bytes per
-// flop and, since the hi / lo split doubles every X operand, reads the fewest LDS
-// bytes per MFMA with wave tiles twice as wide as tall.  Order: the blocks of XCD k
-// (workgroups go to the 8 XCDs round-robin) take groups of GR row blocks k, k+8, ...
-// and walk the column blocks with the group's rows fastest, so the group's X rows stay
-// in the XCD's L2 across the columns and each weight tile is used by the whole group
-// while it is resident.
-constexpr int kBigBK = 32, kBigLD = kBigBK + 8, kBigMaxGainK = 4096;
-
-template <int WM, int WN, int TI, int TJ>
-struct BigTile {
-  static constexpr int threads = 64 * WM * WN, BM = 32 * TI * WM, BN = 32 * TJ * WN;
-  static_assert(BM == threads / 2 && BN == threads / 2, "four X row pieces and two weight row pieces per thread");
-};
-using BigTile128 = BigTile<2, 2, 2, 2>;
-using BigTile256 = BigTile<4, 2, 2, 4>;
-
-template <int WM, int WN, int TI, int TJ, bool NORM>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mfma_big_kernel(Linear L, int gr) {
-  using T = BigTile<WM, WN, TI, TJ>;
-  constexpr int BM = T::BM, BN = T::BN, NT = T::threads, BK = kBigBK, LD = kBigLD;
-  __shared__ __attribute__((aligned(16))) uint16_t Ah[2][BM * LD];
-  __shared__ __attribute__((aligned(16))) uint16_t Al[2][BM * LD];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BN * LD];
-  __shared__ float rs[BM];
-  __shared__ __attribute__((aligned(16))) float gs[NORM ? kBigMaxGainK : 4];  // the norm gain (one vector for every row)
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  int bx = blockIdx.x, by = blockIdx.y;
-  {
-    const int rb = gridDim.y, cb = gridDim.x;
-    if (gr > 0 && rb % (8 * gr) == 0) {
-      const int bid = blockIdx.y * cb + blockIdx.x, xcd = bid & 7, l = bid >> 3;
-      const int g = l / (gr * cb), rem = l - g * gr * cb;
-      bx = rem / gr;
-      by = xcd + 8 * (g * gr + rem % gr);
-    }
-  }
-  const int m0 = by * BM, n0 = bx * BN;
-  // loads in row order: eight lanes read the 128 bytes of one X row's step (rows
-  // t / 8 + NT / 8 * v), four lanes the 64 bytes of one weight row's step (rows
-  // t / 4 + NT / 4 * u), so each load instruction covers whole lines of few rows.  Rows
-  // past M load row 0 of X: their results are finite and never stored (an output row
-  // depends only on its own X row, and so does its sum of squares).
-  constexpr int AR = NT / 8, BR = NT / 4;
-  const int ar = tid >> 3, ak = (tid & 7) * 4, br = tid >> 2, bk = (tid & 3) * 8;
-  const float* arow[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int m = m0 + ar + AR * v;
-    arow[v] = L.X + (size_t)(m < L.M ? (L.xidx ? L.xidx[m] : m) : 0) * L.ldx + ak;
-  }
-  if (NORM)
-    for (int k = tid * 4; k < L.K; k += NT * 4) *reinterpret_cast<float4*>(&gs[k]) = *reinterpret_cast<const float4*>(L.gain + k);
-  // Pair epilogues (SwiGLU over interleaved gate / up rows, RoPE over (even, odd)
-  // columns of q and k) take columns (2p, 2p + 1) together.  Their weight rows are
-  // staged so that the first half of each wave's 32 TJ columns holds the even columns
-  // and the second half their odd partners: each lane then holds both values of its
-  // pairs.  Tile column c is global column n0 + 32 TJ (c / 32 TJ) + 2 (c % 16 TJ) +
-  // (c / 16 TJ) % 2.
-  const bool pair = L.epi.kind == EPI_SWIGLU || L.epi.kind == EPI_QKV;
-  auto bcol = [&](int c) {
-    if (!pair) return n0 + c;
-    const int cc = c % (32 * TJ);
-    return n0 + (c - cc) + 2 * (cc % (16 * TJ)) + cc / (16 * TJ);
-  };
-  const uint16_t* brow0 = mat_row<uint16_t>(L.mats, bcol(br), L.K) + bk;
-  const uint16_t* brow1 = mat_row<uint16_t>(L.mats, bcol(br + BR), L.K) + bk;
-  float ss[4] = {0.f, 0.f, 0.f, 0.f};
-  struct Fetch {
-    float4 a[4];
-    uint4 b0, b1;
-  };
-  Fetch f0, f1;
-  auto fetch = [&](Fetch& f, int k0) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) f.a[v] = *reinterpret_cast<const float4*>(arow[v] + k0);
-    f.b0 = *reinterpret_cast<const uint4*>(brow0 + k0);
-    f.b1 = *reinterpret_cast<const uint4*>(brow1 + k0);
-  };
-  // w = 1 adds the step to the sums of squares, w = 0 (a restaged last step) does not
-  auto stage = [&](const Fetch& f, int k0, int buf, float w) {
-    float4 g;
-    if (NORM) g = *reinterpret_cast<const float4*>(&gs[k0 + ak]);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      float4 t = f.a[v];
-      if (NORM) {
-        ss[v] = fmaf(t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w, w, ss[v]);
-        t.x *= g.x; t.y *= g.y; t.z *= g.z; t.w *= g.w;
-      }
-      uint32_t p0, p1, q0, q1;
-      bf16_hi_lo2(t.x, t.y, p0, q0);
-      bf16_hi_lo2(t.z, t.w, p1, q1);
-      const int off = (ar + AR * v) * LD + ak;
-      *reinterpret_cast<uint2*>(&Ah[buf][off]) = make_uint2(p0, p1);
-      *reinterpret_cast<uint2*>(&Al[buf][off]) = make_uint2(q0, q1);
-    }
-    *reinterpret_cast<uint4*>(&Bs[buf][br * LD + bk]) = f.b0;
-    *reinterpret_cast<uint4*>(&Bs[buf][(br + BR) * LD + bk]) = f.b1;
-  };
-  const int wm = wave / WN, wn = wave % WN;
-  f32x16 acc[TI][TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  auto mfmas = [&](int cur) {
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 16) {
-      bf16x8 fh[TI], fl[TI], fb[TJ];
-#pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        const int off = (wm * 32 * TI + i * 32 + (lane & 31)) * LD + ks + (lane >> 5) * 8;
-        fh[i] = *reinterpret_cast<const bf16x8*>(&Ah[cur][off]);
-        fl[i] = *reinterpret_cast<const bf16x8*>(&Al[cur][off]);
-      }
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-        fb[j] = *reinterpret_cast<const bf16x8*>(&Bs[cur][(wn * 32 * TJ + j * 32 + (lane & 31)) * LD + ks + (lane >> 5) * 8]);
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fh[i], fb[j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fl[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-    }
-  };
-  const int nk = L.K / BK;  // >= 2, even
-  fetch(f0, 0);
-  fetch(f1, BK);
-  __syncthreads();  // the gain vector
-  stage(f0, 0, 0, 1.f);
-  __syncthreads();
-  // step kt: request step kt + 2, run step kt's MFMAs, stage step kt + 1 (fetched a
-  // step earlier) into the other LDS stage
-  // (nk is even: two steps per iteration, each register set and LDS stage in a fixed
-  // place).  The requests and the staging are unconditional (past the end the last step
-  // is re-read and restaged, unused): a load or a staging under a branch splits the
-  // loop body, and the compiler then waits for every load at the join (the current
-  // step's request included, which leaves one step of prefetch) and cannot interleave
-  // the staging with the MFMAs.
-  constexpr bool stage_first = WM * WN == 8;
-  const int klast = (nk - 1) * BK;
-  for (int kt = 0; kt < nk; kt += 2) {
-    fetch(f0, min((kt + 2) * BK, klast));
-    if constexpr (stage_first) {
-      stage(f1, (kt + 1) * BK, 1, 1.f);
-      mfmas(0);
-    } else {
-      mfmas(0);
-      stage(f1, (kt + 1) * BK, 1, 1.f);
-    }
-    __syncthreads();
-    fetch(f1, min((kt + 3) * BK, klast));
-    const float w = kt + 2 < nk ? 1.f : 0.f;
-    if constexpr (stage_first) {
-      stage(f0, min((kt + 2) * BK, klast), 0, w);
-      mfmas(1);
-    } else {
-      mfmas(1);
-      stage(f0, min((kt + 2) * BK, klast), 0, w);
-    }
-    __syncthreads();
-  }
-  // the eight threads of a staged row hold its sum of squares over K
-  if (NORM) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      float t = ss[v];
-      t += xor_lane<1>(t);
-      t += xor_lane<2>(t);
-      t += xor_lane<4>(t);
-      if ((tid & 7) == 0) rs[ar + AR * v] = 1.0f / sqrtf(t / (float)L.K + L.eps);
-    }
-  }
-  __syncthreads();
-  const int jj = lane & 31;
-  // The epilogue branches on its kind once per block.  Every accumulator block is
-  // named by constant indices, inline (a loop the compiler leaves rolled, or an
-  // out-of-line call, would move acc to scratch memory).  Row of element r of block i:
-  auto row_of = [&](int i, int r) { return wm * 32 * TI + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
-  // Rows outer, column blocks inner, so a row's scale and address are computed once.
-  auto each = [&](auto&& f) __attribute__((always_inline)) {
-    static_for<TI>([&](auto ic) __attribute__((always_inline)) {
-      constexpr int i = decltype(ic)::value;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ml = row_of(i, r);
-        const float sc = NORM ? rs[ml] : 1.0f;
-        static_for<TJ>([&](auto jc) __attribute__((always_inline)) {
-          constexpr int j = decltype(jc)::value;
-          f(m0 + ml, n0 + wn * 32 * TJ + j * 32 + jj, acc[i][j][r] * sc);
-        });
-      }
-    });
-  };
-  // pairs: lane value of block j and of block j + TJ / 2 are columns (n, n + 1)
-  auto each_pair = [&](auto&& f) __attribute__((always_inline)) {
-    constexpr int TH = TJ / 2;
-    static_for<TI>([&](auto ic) __attribute__((always_inline)) {
-      constexpr int i = decltype(ic)::value;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ml = row_of(i, r);
-        const float sc = NORM ? rs[ml] : 1.0f;
-        static_for<TH>([&](auto jc) __attribute__((always_inline)) {
-          constexpr int j = decltype(jc)::value;
-          f(m0 + ml, n0 + wn * 32 * TJ + 2 * (j * 32 + jj), acc[i][j][r] * sc, acc[i][j + TH][r] * sc);
-        });
-      }
-    });
-  };
-  // A tile with no row past M stores without a check per element (the check is a
-  // branch around each store).  The output pointer is held in registers (the compiler
-  // reloads kernel arguments after every store through a plain pointer).
-  float* const Y = L.epi.Y;
-  const size_t ldy = (size_t)L.epi.ldy;
-  const bool full = m0 + BM <= L.M;
-  if (L.epi.kind == EPI_SWIGLU) {
-    if (full)
-      each_pair([&](int m, int n, float a0, float a1) __attribute__((always_inline)) {
-        Y[(size_t)m * ldy + (n >> 1)] = silu_fast(a0) * a1;
-      });
-    else
-      each_pair([&](int m, int n, float a0, float a1) __attribute__((always_inline)) {
-        if (m < L.M) Y[(size_t)m * ldy + (n >> 1)] = silu_fast(a0) * a1;
-      });
-  } else if (L.epi.kind == EPI_QKV) {
-    const Epi e = L.epi;
-    if (full)
-      each_pair([&](int m, int n, float a0, float a1) __attribute__((always_inline)) { epi_pair(e, m, n, a0, a1); });
-    else
-      each_pair([&](int m, int n, float a0, float a1) __attribute__((always_inline)) {
-        if (m < L.M) epi_pair(e, m, n, a0, a1);
-      });
-  } else if (L.epi.kind == EPI_STORE) {
-    if (full)
-      each([&](int m, int n, float v) __attribute__((always_inline)) { Y[(size_t)m * ldy + n] = v; });
-    else
-      each([&](int m, int n, float v) __attribute__((always_inline)) {
-        if (m < L.M) Y[(size_t)m * ldy + n] = v;
-      });
-  } else if (L.epi.kind == EPI_RESID) {
-    if (full)
-      each([&](int m, int n, float v) __attribute__((always_inline)) { Y[(size_t)m * ldy + n] += v; });
-    else
-      each([&](int m, int n, float v) __attribute__((always_inline)) {
-        if (m < L.M) Y[(size_t)m * ldy + n] += v;
-      });
-  }
-}
-
 // ------------------------------------------------------------- attention ------
 // Decode attention: block (split s, head h, query i) of four waves covers keys
 // [s*chunk, (s+1)*chunk); wave w takes 64-key steps starting at s*chunk + 64w.  G
@@ -979,7 +726,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(Attn a, int chunk, int
       }
     }
     if (S == 1) {
-      a.O[(size_t)i * a.ldo + h * DH + tid] = den > 0.f ? num / den : 0.f;
+      store_o(a.O, a.ldo, a.split, i, h * DH + tid, den > 0.f ? num / den : 0.f);
     } else {
       float* pp = part + (((size_t)i * a.H + h) * S + s) * (DH + 2);
       pp[tid] = num;
@@ -994,7 +741,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(Attn a, int chunk, int
 // Merge of the S split partials of each (query, head) when it is not done inside the
 // decode kernel.
 template <int DH>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* part, int S, int H, float* O, int ldo) {
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* part, int S, int H, float* O, int ldo, int split) {
   __shared__ float sm[kMaxSplits], sw[kMaxSplits];
   const int h = blockIdx.x, i = blockIdx.y, tid = threadIdx.x;
   const float* pb = part + ((size_t)i * H + h) * S * (DH + 2);
@@ -1013,7 +760,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* part, int 
         den += w * pb[(size_t)t * (DH + 2) + DH + 1];
       }
     }
-    O[(size_t)i * ldo + h * DH + tid] = den > 0.f ? num / den : 0.f;
+    store_o(O, ldo, split, i, h * DH + tid, den > 0.f ? num / den : 0.f);
   }
 }
 
@@ -1110,9 +857,8 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(Attn a, const int32_t
     }
   }
   if (r < cnt) {
-    float* op = a.O + (size_t)(t0 + r) * a.ldo + h * DH + cq * OD;
 #pragma unroll
-    for (int od = 0; od < OD; ++od) op[od] = o[od] / l_run;
+    for (int od = 0; od < OD; ++od) store_o(a.O, a.ldo, a.split, t0 + r, h * DH + cq * OD + od, o[od] / l_run);
   }
 }
 
@@ -1134,13 +880,14 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // two MFMAs each), so their rounding stays near float32; K and V are the cache's own
 // float16 values, staged in LDS as [key][dim] and [dim][key].
 // MFMA operand layout: lane l supplies row / column l % 32 and the 8 k positions
-// 8 (l / 32) .. +7 of each 16-wide k step.  Three waves per SIMD: 168 VGPRs and 8 bytes
-// of scratch (two waves per SIMD need no scratch and measure slower).
+// 8 (l / 32) .. +7 of each 16-wide k step.  K tiles are loaded straight to LDS one block
+// ahead (no registers hold them).  Three waves per SIMD: 168 VGPRs and 8 bytes of scratch
+// (two waves per SIMD need no scratch and measure slower).
 constexpr int kPrefillSplitBelow = 3072;  // blocks of the one-group grid
 
-template <int KG>
+template <int KG, bool SPLIT>
 __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, const int32_t* tiles) {
-  constexpr int DH = 64, LD = DH + 8;
+  constexpr int DH = 64, LD = DH + 8, KT = 64 * DH;  // LD: pitch of the transposed V tile
   // XCD-aware order (workgroups go to the 8 XCDs round-robin by linear id): with a
   // multiple of 8 heads, XCD k takes heads k, k+8, ..., so it reads only their keys and
   // values, which its L2 can hold
@@ -1158,10 +905,11 @@ __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, 
   const int t0 = tiles[2 * tile], cnt = tiles[2 * tile + 1];
   const int b = a.tok.b[t0], slot0 = a.tok.slot[t0];
   const int kvmax = slot0 + cnt;
-  __shared__ __attribute__((aligned(16))) _Float16 kvs[KG][2][64 * LD];
+  // two K tiles per group ([key][dim], 128-byte rows whose 16-byte chunks are stored
+  // XOR-ed with (key / 2) % 8) and one transposed V tile
+  __shared__ __attribute__((aligned(1024))) _Float16 kvs[KG][2 * KT + 64 * LD];
   __shared__ int32_t Gsa[KG][64];
-  _Float16* Ks = kvs[grp][0];
-  _Float16* Vt = kvs[grp][1];
+  _Float16* Vt = kvs[grp] + 2 * KT;
   int32_t* Gs = Gsa[grp];
   const int32_t* gt = a.grp_tab != nullptr ? a.grp_tab + (size_t)b * a.cap : nullptr;
   int k_begin = 0;
@@ -1206,36 +954,37 @@ __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, 
   }
   float m_run = -INFINITY, l_run = 0.f;
   const int nkb = (kvmax - k_begin + 63) / 64;  // >= 1
+  // K tiles go straight to LDS, the next one while this one is used: piece p of a tile is
+  // keys 8 p .. +7, four pieces per wave (rows past kvmax repeat the last visible one)
+  const uint32_t kdst = __builtin_amdgcn_readfirstlane(lds_addr(kvs[grp]) + (uint32_t)qw * 4096);
+  auto load_k = [&](int blk, int buf) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int c = qw * 32 + p * 8 + (lane >> 3), j = min(k_begin + 64 * blk + c, kvmax - 1);
+      dma16(kdst + (uint32_t)buf * (KT * 2) + p * 1024, (uint32_t)j * 128 + (((lane & 7) ^ ((c >> 1) & 7)) * 16),
+            reinterpret_cast<const char*>(kb));
+    }
+  };
+  load_k(min(grp, nkb - 1), 0);
   for (int it = 0; it < (nkb + KG - 1) / KG; ++it) {
     // every group stages a block in every round (past its last one, a valid block it
     // does not use), so that all waves meet at the same barriers
-    const int kbi = it * KG + grp;
+    const int kbi = it * KG + grp, cur = it & 1;
     const int k0 = k_begin + 64 * min(kbi, nkb - 1);
     __syncthreads();  // the previous block's K and V are consumed
     // every load first, unconditionally (a load under a branch is waited for at once):
     // keys past kvmax read the last visible row, a written cache entry, and are masked
     // out of the softmax (probability 0 times a finite value)
     const int32_t gl = gt != nullptr ? gt[min(k0 + (gtid & 63), kvmax - 1)] : 0;
-    // keys: eight lanes per 128-byte row (item i: key idx / 8, dims 8 (idx % 8) ..);
     // values: a lane takes keys 2q, 2q + 1 of one 8-dim part p (q fastest across lanes),
     // so that each transposed write is one 4-byte word holding both keys' values of a
     // dim, and the 32 lanes of a part write 32 different banks
-    uint4 kv4[4], vv4[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = gtid + 128 * i, c = idx >> 3, part = idx & 7, j = min(k0 + c, kvmax - 1);
-      kv4[i] = *reinterpret_cast<const uint4*>(kb + (size_t)j * DH + part * 8);
-    }
+    uint4 vv4[4];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int iu = gtid + 128 * u, q = iu & 31, pp = iu >> 5;
       vv4[2 * u] = *reinterpret_cast<const uint4*>(vb + (size_t)min(k0 + 2 * q, kvmax - 1) * DH + pp * 8);
       vv4[2 * u + 1] = *reinterpret_cast<const uint4*>(vb + (size_t)min(k0 + 2 * q + 1, kvmax - 1) * DH + pp * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = gtid + 128 * i, c = idx >> 3, part = idx & 7;
-      *reinterpret_cast<uint4*>(&Ks[c * LD + part * 8]) = kv4[i];
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -1251,7 +1000,10 @@ __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, 
       }
     }
     if (gtid < 64) Gs[gtid] = k0 + gtid < kvmax ? gl : 0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the K tile has landed
     __syncthreads();
+    load_k(min((it + 1) * KG + grp, nkb - 1), cur ^ 1);
+    const _Float16* Ks = kvs[grp] + cur * KT;
     if (kbi >= nkb) continue;
     // S^T blocks: keys 32 cb + (row of the accumulator), this lane's query
     f32x16 s[2];
@@ -1261,7 +1013,7 @@ __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, 
       for (int r = 0; r < 16; ++r) s[cb][r] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
-        const f16x8 kf = *reinterpret_cast<const f16x8*>(&Ks[(32 * cb + col) * LD + ks * 16 + half * 8]);
+        const f16x8 kf = *reinterpret_cast<const f16x8*>(&Ks[(32 * cb + col) * DH + ((2 * ks + half) ^ ((col >> 1) & 7)) * 8]);
         s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qh[ks], s[cb], 0, 0, 0);
         s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[ks], s[cb], 0, 0, 0);
       }
@@ -1330,11 +1082,12 @@ __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, 
       }
   }
   if constexpr (KG > 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the unused last K tile: its LDS is reused
     // merge: groups 1.. leave (max, sum, unnormalized output) per lane in the LDS that
     // held their K/V tiles ([KG - 1][2 waves][34][64] floats, lane fastest); group 0
     // folds them into its own state
     __syncthreads();
-    float* mbuf = reinterpret_cast<float*>(&kvs[0][0][0]);
+    float* mbuf = reinterpret_cast<float*>(&kvs[0][0]);
     if (grp > 0) {
       float* w = mbuf + (size_t)((grp - 1) * 2 + qw) * 34 * 64 + lane;
       w[0] = m_run;
@@ -1363,9 +1116,24 @@ __global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, 
       m_run = mn;
     }
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land after the block has ended
   if (qi < cnt) {
-    float* op = a.O + (size_t)(t0 + qi) * a.ldo + h * DH;
     const float inv = 1.0f / l_run;
+    if constexpr (SPLIT) {
+      // the head's 64 dims are two groups of a split row; four consecutive dims per store
+      char* op = reinterpret_cast<char*>(a.O + (size_t)(t0 + qi) * a.ldo + h * DH) + 8 * half;
+      static_for<8>([&](auto rc) {
+        constexpr int r = 4 * (decltype(rc)::value & 3), g = decltype(rc)::value >> 2;
+        const f32x16& o = g ? o1 : o0;
+        uint32_t h0, h1, l0, l1;
+        bf16_hi_lo2(o[r] * inv, o[r + 1] * inv, h0, l0);
+        bf16_hi_lo2(o[r + 2] * inv, o[r + 3] * inv, h1, l1);
+        *reinterpret_cast<uint2*>(op + 128 * g + 4 * r) = make_uint2(h0, h1);
+        *reinterpret_cast<uint2*>(op + 128 * g + 64 + 4 * r) = make_uint2(l0, l1);
+      });
+      return;
+    }
+    float* op = a.O + (size_t)(t0 + qi) * a.ldo + h * DH;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int dd = 8 * (r >> 2) + 4 * half + (r & 3);
@@ -1583,7 +1351,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_mq_kernel(Attn a, int chun
     }
     const int i = t0 + q;
     if (S == 1) {
-      a.O[(size_t)i * a.ldo + h * DH + dd] = den > 0.f ? num / den : 0.f;
+      store_o(a.O, a.ldo, a.split, i, h * DH + dd, den > 0.f ? num / den : 0.f);
     } else {
       float* pp = part + (((size_t)i * a.H + h) * S + s) * (DH + 2);
       pp[dd] = num;
@@ -2192,32 +1960,8 @@ hipError_t rows_launch(const Linear& L, hipStream_t st, const Ev& ev) {
   return ns == 4 ? rows_launch_t<2, 4>(L, st, ev) : ns == 2 ? rows_launch_t<2, 2>(L, st, ev) : rows_launch_t<2, 1>(L, st, ev);
 }
 
-template <int WM, int WN, int TI, int TJ>
-hipError_t big_launch_t(BigTile<WM, WN, TI, TJ>, const Linear& L, hipStream_t st, const Ev& ev) {
-  using T = BigTile<WM, WN, TI, TJ>;
-  // row blocks per L2 group: about 2 MiB of float32 X rows
-  const int gr = std::max(1, std::min(8, (int)((2 << 20) / ((int64_t)T::BM * L.K * 4))));
-  const dim3 grid(L.N / T::BN, (L.M + T::BM - 1) / T::BM);
-  if (L.gain != nullptr)
-    return klaunch(gemm_mfma_big_kernel<WM, WN, TI, TJ, true>, grid, dim3(T::threads), 0, st, ev.start, ev.stop, L, gr);
-  return klaunch(gemm_mfma_big_kernel<WM, WN, TI, TJ, false>, grid, dim3(T::threads), 0, st, ev.start, ev.stop, L, gr);
-}
-
-template <typename T>
-hipError_t big_launch(const Linear& L, hipStream_t st, const Ev& ev) {
-  return big_launch_t(T{}, L, st, ev);
-}
-
 template <typename W>
 hipError_t linear_t(const Linear& L, float* inv_rms, hipStream_t st, const Ev& ev) {
-  // large M: the 256x256 tile once its grid fills every compute unit twice, else the
-  // 128x128 tile once its grid fills every compute unit
-  if (mfma_fits<W>(L) && L.K % (2 * kBigBK) == 0 && L.gain2 == nullptr && (L.gain == nullptr || L.K <= kBigMaxGainK)) {
-    if (L.N % BigTile256::BN == 0 && (int64_t)(L.N / BigTile256::BN) * ((L.M + BigTile256::BM - 1) / BigTile256::BM) >= 512)
-      return big_launch<BigTile256>(L, st, ev);
-    if (L.N % BigTile128::BN == 0 && (int64_t)(L.N / BigTile128::BN) * ((L.M + BigTile128::BM - 1) / BigTile128::BM) >= 256)
-      return big_launch<BigTile128>(L, st, ev);
-  }
   if (rows_fits<W>(L)) return rows_launch(L, st, ev);
   if (mfma_fits<W>(L)) {
     // split K until about kMfmaTargetBlocks blocks stream the weights (the partials
@@ -2231,9 +1975,7 @@ hipError_t linear_t(const Linear& L, float* inv_rms, hipStream_t st, const Ev& e
     const dim3 grid(L.N / 64, (L.M + 63) / 64, ks);
     hipError_t e = klaunch(gemm_mfma_kernel, grid, dim3(256), 0, st, ev.start, ks > 1 ? nullptr : ev.stop, L, ks);
     if (e != hipSuccess || ks == 1) return e;
-    const bool pair = L.epi.kind == EPI_SWIGLU || L.epi.kind == EPI_QKV;
-    const int64_t items = (int64_t)L.M * (pair ? L.N / 2 : L.N);
-    return klaunch(gemm_finish_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, nullptr, ev.stop, L, ks);
+    return launch_gemm_finish(L, ks, st, ev);
   }
   if (gemv_fits<W>(L)) {
     switch (L.K / (64 * WT<W>::VEC)) {
@@ -2270,7 +2012,7 @@ hipError_t attn_decode_dh(const Attn& a, int max_kv, float* part, int64_t part_f
                          part);
   if (e != hipSuccess) return e;
   return klaunch(attn_merge_kernel<DH>, dim3(a.H, M), dim3(256), 0, st, nullptr, ev.stop, (const float*)part, S, a.H,
-                 a.O, a.ldo);
+                 a.O, a.ldo, a.split);
 }
 
 // The multi-query kernel: splits sized so that about 2048 blocks (splits x heads x
@@ -2295,7 +2037,7 @@ hipError_t attn_decode_mq(const Attn& a, int max_kv, float* part, int64_t part_f
                          chunk, S, part);
   if (e != hipSuccess) return e;
   return klaunch(attn_merge_kernel<DH>, dim3(a.H, M), dim3(256), 0, st, nullptr, ev.stop, (const float*)part, S, a.H,
-                 a.O, a.ldo);
+                 a.O, a.ldo, a.split);
 }
 
 template <typename KV>
@@ -2318,15 +2060,22 @@ hipError_t attn_prefill_t(const Attn& a, const int32_t* tiles, int ntiles, hipSt
       // a grid that fills the compute units a few times over runs each tile's keys in one
       // group; a smaller one (one long sequence) splits them over two groups, since its
       // last tiles' key chains would otherwise set the kernel's time
-      if ((int64_t)ntiles * a.H < kPrefillSplitBelow)
-        return klaunch(attn_prefill_mfma_kernel<2>, grid, dim3(256), 0, st, ev.start, ev.stop, a, tiles);
-      return klaunch(attn_prefill_mfma_kernel<1>, grid, dim3(128), 0, st, ev.start, ev.stop, a, tiles);
+      const bool two = (int64_t)ntiles * a.H < kPrefillSplitBelow;
+      auto kern = a.split ? (two ? attn_prefill_mfma_kernel<2, true> : attn_prefill_mfma_kernel<1, true>)
+                          : (two ? attn_prefill_mfma_kernel<2, false> : attn_prefill_mfma_kernel<1, false>);
+      return klaunch(kern, grid, dim3(two ? 256 : 128), 0, st, ev.start, ev.stop, a, tiles);
     }
   if (a.dh == 64) return klaunch(attn_prefill_kernel<KV, 64>, grid, dim3(256), 0, st, ev.start, ev.stop, a, tiles);
   return klaunch(attn_prefill_kernel<KV, 32>, grid, dim3(256), 0, st, ev.start, ev.stop, a, tiles);
 }
 
 }  // namespace
+
+hipError_t launch_gemm_finish(const Linear& L, int ks, hipStream_t st, const Ev& ev) {
+  const bool pair = L.epi.kind == EPI_SWIGLU || L.epi.kind == EPI_QKV;
+  const int64_t items = (int64_t)L.M * (pair ? L.N / 2 : L.N);
+  return klaunch(gemm_finish_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, nullptr, ev.stop, L, ks);
+}
 
 bool linear_is_gemv(const Linear& L, int wdt) {
   return wdt ? (!mfma_fits<uint16_t>(L) && gemv_fits<uint16_t>(L)) : gemv_fits<float>(L);

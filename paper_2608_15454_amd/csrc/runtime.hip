@@ -553,7 +553,34 @@ double linear_bytes(const mbp_handle* h, const Linear& L) {
   return N * K * wb + M * K * 4 + out;
 }
 
+// L on split input rows x (L.X and L.gain are not read); y: where a SwiGLU's rows go.
+int run_planes(mbp_handle* h, const Linear& L, const uint16_t* x, uint16_t* y, const Scratch& sc, hipStream_t st) {
+  PlaneLinear P{};
+  P.x = x; P.ldx = L.ldx; P.M = L.M; P.K = L.K; P.N = L.N; P.mats = L.mats; P.kind = L.epi.kind; P.epi = L.epi;
+  P.y = y; P.ldy = L.epi.ldy; P.part = sc.gpart;
+  TIMED(h, MBP_KCLASS_GEMM, linear_bytes(h, L), launch_planes, P, st);
+  return MBP_OK;
+}
+
+// A product of many rows that no epilogue ties to the layers (the unembedding of a long
+// pass, the MLP heads of a large batch) splits its rows first; sc.O is free then.
+constexpr int kSplitFirstRows = 1024;
+
+bool planes_ok(const mbp_handle* h, const Linear& L) {
+  if (!h->wdt || !planes_fit(L.M, L.N, L.K, L.mats.mode == MAT_QKV ? L.mats.rows : L.N)) return false;
+  // the weights go to LDS in 16-byte pieces
+  for (int i = 0; i < (L.mats.mode == MAT_QKV ? 3 : L.mats.mode == MAT_GATEUP ? 2 : 1); ++i)
+    if (reinterpret_cast<uintptr_t>(L.mats.m[i]) % 16 != 0) return false;
+  return true;
+}
+
 int run_linear(mbp_handle* h, Linear L, const Scratch& sc, hipStream_t st) {
+  if (L.M >= kSplitFirstRows && L.epi.kind == EPI_STORE && L.xidx == nullptr && L.gain2 == nullptr && L.K == h->sz.d &&
+      L.ldx == L.K && planes_ok(h, L)) {
+    uint16_t* so = reinterpret_cast<uint16_t*>(sc.O);
+    OTHER(h, launch_split_rows, L.X, L.gain, L.eps, so, L.K, L.M, st);
+    return run_planes(h, L, so, nullptr, sc, st);
+  }
   L.part = sc.gpart;
   float* inv = sc.inv;
   const int cls = linear_is_gemv(L, h->wdt) ? MBP_KCLASS_GEMV : MBP_KCLASS_GEMM;
@@ -712,6 +739,8 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
   const int M = tok.M;
   if (M == 0) return MBP_OK;
   const float scale = h->cfg.attn_scale / std::sqrt((float)s.dh);
+  uint16_t* const so = reinterpret_cast<uint16_t*>(sc.O);
+  uint16_t* const sh = reinterpret_cast<uint16_t*>(sc.Hid);
   for (size_t l = 0; l < layers.size(); ++l) {
     const BlockW& w = layers[l];
     char* kc = reinterpret_cast<char*>(kv.k) + l * kv.layer_stride * s.es;
@@ -724,11 +753,33 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
     qkv.epi.kind = EPI_QKV; qkv.epi.Q = sc.Q; qkv.epi.kc = kc; qkv.epi.vc = vc;
     qkv.epi.b_stride = kv.b_stride; qkv.epi.cap = kv.cap; qkv.epi.H = s.H; qkv.epi.dh = s.dh; qkv.epi.d = s.d;
     qkv.epi.rope = h->rope; qkv.epi.tok = tok; qkv.epi.kvt = h->cfg.kv_dtype;
-    RCK(run_linear(h, qkv, sc, st));
+    Linear o{};
+    o.X = sc.O; o.ldx = s.d; o.M = M; o.K = s.d; o.N = s.d; o.gain = nullptr;
+    o.mats.m[0] = w.wo; o.mats.rows = s.d; o.mats.mode = MAT_SINGLE;
+    o.epi.kind = EPI_RESID; o.epi.Y = X; o.epi.ldy = s.d;
+    Linear gu{};
+    gu.X = X; gu.ldx = s.d; gu.M = M; gu.K = s.d; gu.N = 2 * s.dff;
+    gu.gain = w.ffn_norm; gu.eps = h->cfg.rms_eps;
+    gu.mats.m[0] = w.wg; gu.mats.m[1] = w.wu; gu.mats.rows = s.dff; gu.mats.mode = MAT_GATEUP;
+    gu.epi.kind = EPI_SWIGLU; gu.epi.Y = sc.Hid; gu.epi.ldy = s.dff;
+    Linear dn{};
+    dn.X = sc.Hid; dn.ldx = s.dff; dn.M = M; dn.K = s.dff; dn.N = s.d; dn.gain = nullptr;
+    dn.mats.m[0] = w.wd; dn.mats.rows = s.d; dn.mats.mode = MAT_SINGLE;
+    dn.epi.kind = EPI_RESID; dn.epi.Y = X; dn.epi.ldy = s.d;
+    // long passes of bfloat16 models run on split rows (PlaneLinear): each linear's input
+    // is split once, by the kernel that produces it, in the place of its float32 rows
+    const bool planes = planes_ok(h, qkv) && planes_ok(h, o) && planes_ok(h, gu) && planes_ok(h, dn);
+
+    if (planes) {
+      OTHER(h, launch_split_rows, X, w.attn_norm, h->cfg.rms_eps, so, s.d, M, st);
+      RCK(run_planes(h, qkv, so, nullptr, sc, st));
+    } else {
+      RCK(run_linear(h, qkv, sc, st));
+    }
 
     Attn a{};
     a.Q = sc.Q; a.ldq = s.d; a.kc = kc; a.vc = vc; a.b_stride = kv.b_stride; a.cap = kv.cap;
-    a.H = s.H; a.dh = s.dh; a.tok = tok; a.grp_tab = grp_tab; a.scale = scale; a.O = sc.O; a.ldo = s.d;
+    a.H = s.H; a.dh = s.dh; a.tok = tok; a.grp_tab = grp_tab; a.scale = scale; a.O = sc.O; a.ldo = s.d; a.split = planes ? 1 : 0;
     const double abytes = kv_rows * 2.0 * s.d * (double)s.es + 2.0 * M * s.d * 4;
     if (tiled) {
       TIMED(h, MBP_KCLASS_ATTN, abytes, launch_attn_prefill, a, h->cfg.kv_dtype, tiles, ntiles, st);
@@ -736,24 +787,14 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
       TIMED(h, MBP_KCLASS_ATTN, abytes, launch_attn_decode, a, h->cfg.kv_dtype, max_kv, sc.part, sc.part_floats, st);
     }
 
-    Linear o{};
-    o.X = sc.O; o.ldx = s.d; o.M = M; o.K = s.d; o.N = s.d; o.gain = nullptr;
-    o.mats.m[0] = w.wo; o.mats.rows = s.d; o.mats.mode = MAT_SINGLE;
-    o.epi.kind = EPI_RESID; o.epi.Y = X; o.epi.ldy = s.d;
-    RCK(run_linear(h, o, sc, st));
-
-    Linear gu{};
-    gu.X = X; gu.ldx = s.d; gu.M = M; gu.K = s.d; gu.N = 2 * s.dff;
-    gu.gain = w.ffn_norm; gu.eps = h->cfg.rms_eps;
-    gu.mats.m[0] = w.wg; gu.mats.m[1] = w.wu; gu.mats.rows = s.dff; gu.mats.mode = MAT_GATEUP;
-    gu.epi.kind = EPI_SWIGLU; gu.epi.Y = sc.Hid; gu.epi.ldy = s.dff;
-    RCK(run_linear(h, gu, sc, st));
-
-    Linear dn{};
-    dn.X = sc.Hid; dn.ldx = s.dff; dn.M = M; dn.K = s.dff; dn.N = s.d; dn.gain = nullptr;
-    dn.mats.m[0] = w.wd; dn.mats.rows = s.d; dn.mats.mode = MAT_SINGLE;
-    dn.epi.kind = EPI_RESID; dn.epi.Y = X; dn.epi.ldy = s.d;
-    RCK(run_linear(h, dn, sc, st));
+    RCK(planes ? run_planes(h, o, so, nullptr, sc, st) : run_linear(h, o, sc, st));
+    if (planes) {
+      OTHER(h, launch_split_rows, X, w.ffn_norm, h->cfg.rms_eps, so, s.d, M, st);
+      RCK(run_planes(h, gu, so, sh, sc, st));
+    } else {
+      RCK(run_linear(h, gu, sc, st));
+    }
+    RCK(planes ? run_planes(h, dn, sh, nullptr, sc, st) : run_linear(h, dn, sc, st));
   }
   return MBP_OK;
 }
@@ -1269,12 +1310,20 @@ int draft(mbp_handle* h, int n, float tau, bool threshold, uint8_t* d_cand, floa
       gu.X = h1; gu.ldx = s.d; gu.M = B; gu.K = s.d; gu.N = 2 * s.dff; gu.gain = w.norm; gu.eps = c.rms_eps;
       gu.mats.m[0] = w.wg; gu.mats.m[1] = w.wu; gu.mats.rows = s.dff; gu.mats.mode = MAT_GATEUP;
       gu.epi.kind = EPI_SWIGLU; gu.epi.Y = sc.Hid; gu.epi.ldy = s.dff;
-      RCK(run_linear(h, gu, sc, h->st));
       Linear dn{};
       dn.X = sc.Hid; dn.ldx = s.dff; dn.M = B; dn.K = s.dff; dn.N = s.d; dn.gain = nullptr;
       dn.mats.m[0] = w.wd; dn.mats.rows = s.d; dn.mats.mode = MAT_SINGLE;
       dn.epi.kind = EPI_RESID; dn.epi.Y = mlp_out + (size_t)m * s.d; dn.epi.ldy = s.nmax * s.d;
-      RCK(run_linear(h, dn, sc, h->st));
+      if (planes_ok(h, gu) && planes_ok(h, dn)) {
+        uint16_t* so = reinterpret_cast<uint16_t*>(sc.O);
+        uint16_t* sh = reinterpret_cast<uint16_t*>(sc.Hid);
+        OTHER(h, launch_split_rows, h1, w.norm, c.rms_eps, so, s.d, B, h->st);
+        RCK(run_planes(h, gu, so, sh, sc, h->st));
+        RCK(run_planes(h, dn, sh, nullptr, sc, h->st));
+      } else {
+        RCK(run_linear(h, gu, sc, h->st));
+        RCK(run_linear(h, dn, sc, h->st));
+      }
     }
   }
   // head: RMSNorm with the head's gain (NT norm for candidate 1, MB norm for the LCA
