@@ -97,14 +97,47 @@ hipError_t klaunch(Kern kernel, dim3 grid, dim3 block, size_t shm, hipStream_t s
 
 // ------------------------------------------------------------------ GEMV ------
 // Wave w of block g owns output rows [(4g+w)*R, +R) and loads its whole R x K weight
-// slice into registers first (lane l holds 16 bytes of every 64*VEC-column chunk),
-// so each weight byte leaves HBM once.  Input rows are processed MR at a time; each
+// slice into registers first (lane l holds VEC columns of every 64*VEC-column chunk: 16
+// bytes, or fewer where K itself is narrower than 64 lanes of 16 bytes), so each weight
+// byte leaves HBM once.  Input rows are processed MR at a time; each
 // lane reads only the slice of the row that matches its weights.  The RMSNorm scale
 // is a per-row scalar, so it is applied after the dot product: the sum of squares
 // accumulates in the same pass.  No LDS and no block-level synchronization.
-template <typename W, int MR, int R, int KC>
+template <typename W, int VEC>
+struct WSlice {  // VEC weights of one row: 4, 8 or 16 bytes
+  static constexpr int NB = VEC * (int)sizeof(W);
+  static_assert(NB == 4 || NB == 8 || NB == 16, "slice bytes");
+  using Raw = std::conditional_t<NB == 16, uint4, std::conditional_t<NB == 8, uint2, uint32_t>>;
+  __device__ static void unpack(const Raw& r, float* f) {
+    if constexpr (NB == 16) {
+      WT<W>::unpack(r, f);
+    } else {
+      uint32_t w[NB / 4];
+      if constexpr (NB == 8) {
+        w[0] = r.x;
+        w[1] = r.y;
+      } else {
+        w[0] = r;
+      }
+#pragma unroll
+      for (int i = 0; i < NB / 4; ++i) {
+        if constexpr (sizeof(W) == 4) {
+          f[i] = __uint_as_float(w[i]);
+        } else {
+          f[2 * i] = bf2f(w[i] & 0xffffu);
+          f[2 * i + 1] = bf2f(w[i] >> 16);
+        }
+      }
+    }
+  }
+};
+
+template <typename W, int MR, int R, int KC, int VEC = WT<W>::VEC>
 __global__ __launch_bounds__(256) void gemv_kernel(Linear L) {
-  constexpr int VEC = WT<W>::VEC;
+  using WS = WSlice<W, VEC>;
+  using Raw = typename WS::Raw;
+  constexpr int XV = VEC < 4 ? VEC : 4;  // input values per load
+  using XT = std::conditional_t<XV == 4, float4, float2>;
   constexpr int K = KC * 64 * VEC;
   constexpr int V = R * MR;     // accumulators per lane
   constexpr int LPV = 64 / V;   // lanes per reduced value
@@ -112,12 +145,12 @@ __global__ __launch_bounds__(256) void gemv_kernel(Linear L) {
   const int n0 = (blockIdx.x * 4 + wave) * R;
   if (n0 >= L.N) return;
 
-  uint4 wv[R][KC];
+  Raw wv[R][KC];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const W* row = mat_row<W>(L.mats, n0 + r, K);
 #pragma unroll
-    for (int c = 0; c < KC; ++c) wv[r][c] = *reinterpret_cast<const uint4*>(row + c * 64 * VEC + lane * VEC);
+    for (int c = 0; c < KC; ++c) wv[r][c] = *reinterpret_cast<const Raw*>(row + c * 64 * VEC + lane * VEC);
   }
   const bool norm = L.gain != nullptr;
 
@@ -142,21 +175,31 @@ __global__ __launch_bounds__(256) void gemv_kernel(Linear L) {
       const int k0 = c * 64 * VEC + lane * VEC;
       float wf[R][VEC];
 #pragma unroll
-      for (int r = 0; r < R; ++r) WT<W>::unpack(wv[r][c], wf[r]);
+      for (int r = 0; r < R; ++r) WS::unpack(wv[r][c], wf[r]);
 #pragma unroll
       for (int m = 0; m < MR; ++m) {
         float xv[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; v += 4) {
-          const float4 t = live[m] ? *reinterpret_cast<const float4*>(xrow[m] + k0 + v) : make_float4(0.f, 0.f, 0.f, 0.f);
-          xv[v] = t.x; xv[v + 1] = t.y; xv[v + 2] = t.z; xv[v + 3] = t.w;
+        for (int v = 0; v < VEC; v += XV) {
+          XT t = *reinterpret_cast<const XT*>(xrow[m] + k0 + v);
+          xv[v] = t.x; xv[v + 1] = t.y;
+          if constexpr (XV == 4) { xv[v + 2] = t.z; xv[v + 3] = t.w; }
+        }
+        if (!live[m]) {
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) xv[v] = 0.f;
         }
         if (norm) {
 #pragma unroll
-          for (int v = 0; v < VEC; v += 4) {
-            const float4 g = *reinterpret_cast<const float4*>(grow[m] + k0 + v);
-            ss[m] += xv[v] * xv[v] + xv[v + 1] * xv[v + 1] + xv[v + 2] * xv[v + 2] + xv[v + 3] * xv[v + 3];
-            xv[v] *= g.x; xv[v + 1] *= g.y; xv[v + 2] *= g.z; xv[v + 3] *= g.w;
+          for (int v = 0; v < VEC; v += XV) {
+            const XT g = *reinterpret_cast<const XT*>(grow[m] + k0 + v);
+            if constexpr (XV == 4) {
+              ss[m] += xv[v] * xv[v] + xv[v + 1] * xv[v + 1] + xv[v + 2] * xv[v + 2] + xv[v + 3] * xv[v + 3];
+              xv[v] *= g.x; xv[v + 1] *= g.y; xv[v + 2] *= g.z; xv[v + 3] *= g.w;
+            } else {
+              ss[m] += xv[v] * xv[v] + xv[v + 1] * xv[v + 1];
+              xv[v] *= g.x; xv[v + 1] *= g.y;
+            }
           }
         }
 #pragma unroll
@@ -1885,10 +1928,19 @@ constexpr int gemv_r(int kc) { return kc <= 4 ? 4 : (kc == 8 ? 2 : 1); }
 // accumulators small
 constexpr int gemv_mr(int kc) { return kc <= 2 ? 4 : (kc <= 8 ? 2 : 1); }
 
+// Columns per lane for K below one chunk of 16-byte lanes: K = 128, and K = 256 of
+// bfloat16 weights (0: K is not that narrow).
+template <typename W>
+constexpr int gemv_narrow_vec(int K) {
+  return K == 128 || (K == 256 && sizeof(W) == 2) ? K / 64 : 0;
+}
+
 template <typename W>
 bool gemv_fits(const Linear& L) {
   constexpr int VEC = WT<W>::VEC;
-  if (L.M > kGemvMaxRows || L.K % (64 * VEC) != 0) return false;
+  if (L.M > kGemvMaxRows) return false;
+  if (gemv_narrow_vec<W>(L.K) != 0) return L.N % 4 == 0;
+  if (L.K % (64 * VEC) != 0) return false;
   const int kc = L.K / (64 * VEC);
   if (kc != 1 && kc != 2 && kc != 4 && kc != 8 && kc != 16) return false;
   const int r = gemv_r(kc);
@@ -1896,16 +1948,16 @@ bool gemv_fits(const Linear& L) {
   return L.N % r == 0 && !(pair && r % 2 != 0);
 }
 
-template <typename W, int KC, int R>
+template <typename W, int KC, int R, int VEC = WT<W>::VEC>
 hipError_t gemv_launch_r(const Linear& L, hipStream_t st, const Ev& ev) {
   constexpr int MRMAX = gemv_mr(KC);
   const dim3 grid((L.N / R + 3) / 4);
-  if (L.M == 1) return klaunch(gemv_kernel<W, 1, R, KC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
+  if (L.M == 1) return klaunch(gemv_kernel<W, 1, R, KC, VEC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
   if constexpr (MRMAX >= 2) {
-    if (L.M == 2 || MRMAX == 2) return klaunch(gemv_kernel<W, 2, R, KC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
+    if (L.M == 2 || MRMAX == 2) return klaunch(gemv_kernel<W, 2, R, KC, VEC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
   }
-  if constexpr (MRMAX >= 4) return klaunch(gemv_kernel<W, 4, R, KC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
-  return klaunch(gemv_kernel<W, 1, R, KC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
+  if constexpr (MRMAX >= 4) return klaunch(gemv_kernel<W, 4, R, KC, VEC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
+  return klaunch(gemv_kernel<W, 1, R, KC, VEC>, grid, dim3(256), 0, st, ev.start, ev.stop, L);
 }
 
 // A narrow product (few output rows, such as the 256-row unembedding) at R rows per
@@ -1978,6 +2030,12 @@ hipError_t linear_t(const Linear& L, float* inv_rms, hipStream_t st, const Ev& e
     return launch_gemm_finish(L, ks, st, ev);
   }
   if (gemv_fits<W>(L)) {
+    // narrow K: these products (models of d = 128, bfloat16 ones of d = 256) used to take
+    // the 64 x 64 tile, whose few blocks walk K alone (N = 384..1024, K = 128: 12.7 us)
+    const int nv = gemv_narrow_vec<W>(L.K);
+    if (nv == 2) return gemv_launch_r<W, 1, 4, 2>(L, st, ev);
+    if constexpr (sizeof(W) == 2)
+      if (nv == 4) return gemv_launch_r<W, 1, 4, 4>(L, st, ev);
     switch (L.K / (64 * WT<W>::VEC)) {
       case 1: return gemv_launch<W, 1>(L, st, ev);
       case 2: return gemv_launch<W, 2>(L, st, ev);
