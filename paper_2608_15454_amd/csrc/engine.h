@@ -100,6 +100,7 @@ struct EAttn {
   float scale;
   int32_t kvt;
   uint64_t* part;  // [M, H, S, dh + 2]
+  uint64_t* out;   // [M, H*dh], S = 1
 };
 
 struct EMerge {

@@ -350,7 +350,7 @@ __device__ __forceinline__ float row_scale(const float* ssw, int m, int K, float
   return 1.0f / sqrtf(ss / (float)K + eps);
 }
 // One dword of every 64-byte line of an operation's descriptor fields, XOR-ed: bytes
-// [8, 200) of the EOp for a linear operation, [200, 296) for attention.  Reading them
+// [8, 200) of the EOp for a linear operation, [200, 304) for attention.  Reading them
 // early brings the lines into the scalar cache, so the fields read later (the
 // epilogue's, or the next operation's) do not each wait for a miss where they are
 // used.  The caller folds the result into a poll tag masked with ECall::zero (0 at
@@ -745,7 +745,9 @@ __device__ __forceinline__ AttnRow attn_row(const ECall& c, int i) {
 // takes steps of KW keys from lo + KW*(w-1); G lanes share a key row (VEC elements
 // each), so one load round covers 64/G keys and a step is eight rounds.  On the
 // split over this pass's keys (read from kvn), waves 1..EW-1 take one load round
-// each.  The waves' (max, sum,
+// each.  With one split per (row, head) (short contexts), the block takes all cached
+// keys on waves 1..EW-1 and this pass's keys on wave 0, and writes the output itself:
+// the partials' trip to the merge operation and its own step are saved.  The waves' (max, sum,
 // numerator) are combined in LDS and the block writes one partial.  r0: the rows of
 // the block's first item (it = the block index), loaded once per launch.
 // Softmax exps are __expf (v_exp_f32 on x log2 e), as in the per-kernel attention.
@@ -774,9 +776,10 @@ __device__ __forceinline__ void op_attn(const EAttn& a, const ECall& c, uint32_t
     const int b = rw.b, kvlen = rw.kvlen, ns = rw.ns, gq = rw.gq;
     const int f = gld(c.first + i);
     const int32_t* gt = c.grp_tab != nullptr ? c.grp_tab + (size_t)b * a.cap : nullptr;
-    const bool fresh = s == S - 1;
+    const bool whole = S == 1;
+    const bool fresh = !whole && s == S - 1;
     const int lo = fresh ? ns : s * c.chunk;
-    const int hi = fresh ? kvlen : min(min(lo + c.chunk, ns), kvlen);
+    const int hi = fresh ? kvlen : whole ? min(ns, kvlen) : min(min(lo + c.chunk, ns), kvlen);
     const size_t boff = (size_t)b * a.b_stride + (size_t)h * a.cap * DH + cq * VEC;
     const KV* kb = reinterpret_cast<const KV*>(a.kc) + boff;
     const KV* vb = reinterpret_cast<const KV*>(a.vc) + boff;
@@ -800,6 +803,44 @@ __device__ __forceinline__ void op_attn(const EAttn& a, const ECall& c, uint32_t
         hooked = true;
       }
     };
+    // One load round of this pass's keys: slot jf is row f + (jf - ns) of kvn (float32,
+    // tagged); fin: the lane's key exists.  Updates (m_run, l_run, o).
+    auto own_keys = [&](int jf, bool fin) {
+      float dot = 0.f;
+      float vrow[VEC];
+      if (fin) {
+        const uint64_t* kp = a.kvn + (size_t)(f + jf - ns) * a.kvn_ld + h * DH + cq * VEC;
+        auto ep = [&](int v) { return kp + (v < VEC ? v : a.d + v - VEC); };
+        uint64_t fe[2 * VEC];
+#pragma unroll
+        for (int v = 0; v < 2 * VEC; ++v) fe[v] = ll_load(ep(v));
+        ll_settle<2 * VEC>(fe, ep, (1u << (2 * VEC)) - 1u, ktag, err);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+          dot += q[v] * __uint_as_float((uint32_t)fe[v]);
+          vrow[v] = __uint_as_float((uint32_t)fe[VEC + v]);
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) vrow[v] = 0.f;
+      }
+      dot = group_sum<G>(dot);
+      bool vis = fin;
+      if (vis && gt != nullptr) {
+        const int gj = gld(gt + jf);
+        vis = (gj == gq) || (gj == gq - 1);
+      }
+      const float sc = vis ? dot : -INFINITY;
+      const float mx = across_max<G>(sc);
+      if (mx == -INFINITY) return;  // wave-uniform
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
+      const float p = vis ? __expf(sc - m_new) : 0.f;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) o[v] = o[v] * alpha + p * vrow[v];
+      l_run = l_run * alpha + p;
+      m_run = m_new;
+    };
     // The two kinds of split run in separate branches (fresh is the same for the whole
     // block), each with its own barrier, so their prefetched registers do not overlap.
     if (!fresh) {
@@ -815,6 +856,8 @@ __device__ __forceinline__ void op_attn(const EAttn& a, const ECall& c, uint32_t
       }
       lds_barrier();
       take_q();
+      if (whole && wave == 0)
+        for (int jf = ns; jf < kvlen; jf += KPR) own_keys(jf + g, jf + g < kvlen && f + jf + g - ns < c.M);
       for (; j0 < hi; j0 += (EW - 1) * KW) {
         if (j0 != lo + (wave - 1) * KW) {
 #pragma unroll
@@ -871,41 +914,7 @@ __device__ __forceinline__ void op_attn(const EAttn& a, const ECall& c, uint32_t
       if (wave == 0) poll_q();
       lds_barrier();
       take_q();
-      if (wave >= 1 && lo + (wave - 1) * KPR < hi) {  // wave-uniform: the wave has keys
-        float dot = 0.f;
-        float vrow[VEC];
-        if (fin) {
-          const uint64_t* kp = a.kvn + (size_t)(f + jf - ns) * a.kvn_ld + h * DH + cq * VEC;
-          auto ep = [&](int v) { return kp + (v < VEC ? v : a.d + v - VEC); };
-          uint64_t fe[2 * VEC];
-#pragma unroll
-          for (int v = 0; v < 2 * VEC; ++v) fe[v] = ll_load(ep(v));
-          ll_settle<2 * VEC>(fe, ep, (1u << (2 * VEC)) - 1u, ktag, err);
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) {
-            dot += q[v] * __uint_as_float((uint32_t)fe[v]);
-            vrow[v] = __uint_as_float((uint32_t)fe[VEC + v]);
-          }
-        } else {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) vrow[v] = 0.f;
-        }
-        dot = group_sum<G>(dot);
-        bool vis = fin;
-        if (vis && gt != nullptr) {
-          const int gj = gld(gt + jf);
-          vis = (gj == gq) || (gj == gq - 1);
-        }
-        const float sc = vis ? dot : -INFINITY;
-        const float mx = across_max<G>(sc);
-        if (mx != -INFINITY) {  // wave-uniform
-          const float p = vis ? __expf(sc - mx) : 0.f;
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) o[v] = p * vrow[v];
-          l_run = p;
-          m_run = mx;
-        }
-      }
+      if (wave >= 1 && lo + (wave - 1) * KPR < hi) own_keys(jf, fin);  // wave-uniform: the wave has keys
     }
     // sum over the lanes that share a dimension chunk (different keys, same m_run)
     l_run = across_sum<G>(l_run);
@@ -934,11 +943,15 @@ __device__ __forceinline__ void op_attn(const EAttn& a, const ECall& c, uint32_t
           den += e * wl[w];
         }
       }
-      uint64_t* pp = a.part + (((size_t)i * H + h) * S + s) * (DH + 2);
-      ll_store(pp + tid, num, tag);
-      if (tid == 0) {
-        ll_store(pp + DH, mb, tag);
-        ll_store(pp + DH + 1, den, tag);
+      if (whole) {
+        ll_store(a.out + (size_t)i * (H * DH) + h * DH + tid, den > 0.f ? num / den : 0.f, tag + 1);
+      } else {
+        uint64_t* pp = a.part + (((size_t)i * H + h) * S + s) * (DH + 2);
+        ll_store(pp + tid, num, tag);
+        if (tid == 0) {
+          ll_store(pp + DH, mb, tag);
+          ll_store(pp + DH + 1, den, tag);
+        }
       }
     }
   }
@@ -1086,7 +1099,7 @@ __device__ __forceinline__ void stack_pass(const EOp* __restrict__ ops, int nlay
       weights_ahead(lin(o + 5), pd, g);
     }
     lds_barrier();
-    op_merge<SH::DH>(mrg(o + 2), c, base, base + cops[o + 2].tag, err, g);
+    if (c.S > 1) op_merge<SH::DH>(mrg(o + 2), c, base, base + cops[o + 2].tag, err, g);
     op_linear<W, SH::KCD, SH::NSO, SH::RO, mr_of<SH::RO, SH::KCD / SH::NSO, MULTI>(), false>(
         lin(o + 3), c, base, base + cops[o + 3].tag, err, lds, po, nullptr,
         (touch_lines(cops + o + 3) ^ touch_lines(cops + o + 4)) & c.zero, g, [&] {

@@ -120,3 +120,16 @@ def test_engine_matches_per_kernel_path_d1024():
     print("engine vs per-kernel max logit difference", err)
     assert err < 2e-2 * 8.0
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("batch,length", [(1, 446), (2, 893)])
+def test_engine_attention_splits_edge(batch, length):
+    """Short contexts run a (row, head)'s attention in one block, longer ones in split
+    keys with a merge: steps that cross the line (448 cached keys for one row, 896 for
+    several), for the encoder and NT decoder; the LM module and MB window stay below it."""
+    raw = synth.make_weights(synth.SMALL_F32, seed=5, gain_jitter=0.2, logit_gain=10.0)
+    W = oracle.to_float64(raw)
+    dec = new_decoder(synth.SMALL_F32, raw, batch, 1000)
+    prompts = [synth.make_prompt(20 + b, length - 3 * b) for b in range(batch)]
+    st = forced_run(dec, W, synth.SMALL_F32, prompts, 5, 3, 0.75, tol=base_tol(synth.SMALL_F32) * 10, timing=True)
+    assert st.timing["engine"][0] > 0
