@@ -114,6 +114,12 @@ struct PlaneLinear {
   uint16_t* y;
   int32_t ldy;
   float* part;  // split-K scratch (kGemmPartFloats floats)
+  // RESID: when next is set and K is split, the kernel that adds the parts also writes
+  // the split rows of RMSNorm(Y) * next_gain (rows of N = ldy values), the next linear's
+  // input (planes_plan tells whether K is split)
+  uint16_t* next;
+  const float* next_gain;
+  float eps;
 };
 // Whether a linear of this shape (bfloat16 weights) runs on split rows; n_mat: rows of
 // one matrix of a fused weight (N otherwise).
@@ -125,6 +131,7 @@ struct PlanesPlan {
   int tile, ks;
 };
 PlanesPlan planes_plan(const PlaneLinear& P);
+bool planes_fuses_norm(const PlaneLinear& P);  // whether launch_planes writes P.next
 hipError_t launch_planes_at(const PlaneLinear& P, PlanesPlan plan, hipStream_t st, const Ev& ev = Ev());
 // The sums of ks partial products in L.part and the epilogue (the second half of a
 // split-K launch: only ev.stop is stamped).

@@ -926,10 +926,10 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // 8 (l / 32) .. +7 of each 16-wide k step.  K tiles are loaded straight to LDS one block
 // ahead (no registers hold them).  Three waves per SIMD: 168 VGPRs and 8 bytes of scratch
 // (two waves per SIMD need no scratch and measure slower).
-constexpr int kPrefillSplitBelow = 3072;  // blocks of the one-group grid
+constexpr int kPrefillSplitBelow = 3072, kPrefillFourUpTo = 256;  // blocks of the one-group grid
 
 template <int KG, bool SPLIT>
-__global__ __launch_bounds__(128 * KG, 3) void attn_prefill_mfma_kernel(Attn a, const int32_t* tiles) {
+__global__ __launch_bounds__(128 * KG, KG == 4 ? 2 : 3) void attn_prefill_mfma_kernel(Attn a, const int32_t* tiles) {
   constexpr int DH = 64, LD = DH + 8, KT = 64 * DH;  // LD: pitch of the transposed V tile
   // XCD-aware order (workgroups go to the 8 XCDs round-robin by linear id): with a
   // multiple of 8 heads, XCD k takes heads k, k+8, ..., so it reads only their keys and
@@ -2118,10 +2118,12 @@ hipError_t attn_prefill_t(const Attn& a, const int32_t* tiles, int ntiles, hipSt
       // a grid that fills the compute units a few times over runs each tile's keys in one
       // group; a smaller one (one long sequence) splits them over two groups, since its
       // last tiles' key chains would otherwise set the kernel's time
-      const bool two = (int64_t)ntiles * a.H < kPrefillSplitBelow;
-      auto kern = a.split ? (two ? attn_prefill_mfma_kernel<2, true> : attn_prefill_mfma_kernel<1, true>)
-                          : (two ? attn_prefill_mfma_kernel<2, false> : attn_prefill_mfma_kernel<1, false>);
-      return klaunch(kern, grid, dim3(two ? 256 : 128), 0, st, ev.start, ev.stop, a, tiles);
+      // and one of at most a block per compute unit over four
+      const int64_t blocks = (int64_t)ntiles * a.H;
+      const int kg = blocks <= kPrefillFourUpTo ? 4 : blocks < kPrefillSplitBelow ? 2 : 1;
+      auto kern = a.split ? (kg == 4 ? attn_prefill_mfma_kernel<4, true> : kg == 2 ? attn_prefill_mfma_kernel<2, true> : attn_prefill_mfma_kernel<1, true>)
+                          : (kg == 4 ? attn_prefill_mfma_kernel<4, false> : kg == 2 ? attn_prefill_mfma_kernel<2, false> : attn_prefill_mfma_kernel<1, false>);
+      return klaunch(kern, grid, dim3(128 * kg), 0, st, ev.start, ev.stop, a, tiles);
     }
   if (a.dh == 64) return klaunch(attn_prefill_kernel<KV, 64>, grid, dim3(256), 0, st, ev.start, ev.stop, a, tiles);
   return klaunch(attn_prefill_kernel<KV, 32>, grid, dim3(256), 0, st, ev.start, ev.stop, a, tiles);

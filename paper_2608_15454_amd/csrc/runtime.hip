@@ -554,10 +554,15 @@ double linear_bytes(const mbp_handle* h, const Linear& L) {
 }
 
 // L on split input rows x (L.X and L.gain are not read); y: where a SwiGLU's rows go.
-int run_planes(mbp_handle* h, const Linear& L, const uint16_t* x, uint16_t* y, const Scratch& sc, hipStream_t st) {
+// With next (a residual product): *fused tells whether the split rows of the result's
+// RMSNorm with next_gain were written there too.
+int run_planes(mbp_handle* h, const Linear& L, const uint16_t* x, uint16_t* y, const Scratch& sc, hipStream_t st,
+               uint16_t* next = nullptr, const float* next_gain = nullptr, bool* fused = nullptr) {
   PlaneLinear P{};
   P.x = x; P.ldx = L.ldx; P.M = L.M; P.K = L.K; P.N = L.N; P.mats = L.mats; P.kind = L.epi.kind; P.epi = L.epi;
   P.y = y; P.ldy = L.epi.ldy; P.part = sc.gpart;
+  P.next = next; P.next_gain = next_gain; P.eps = h->cfg.rms_eps;
+  if (fused != nullptr) *fused = next != nullptr && planes_fuses_norm(P);
   TIMED(h, MBP_KCLASS_GEMM, linear_bytes(h, L), launch_planes, P, st);
   return MBP_OK;
 }
@@ -747,6 +752,7 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
   const float scale = h->cfg.attn_scale / std::sqrt((float)s.dh);
   uint16_t* const so = reinterpret_cast<uint16_t*>(sc.O);
   uint16_t* const sh = reinterpret_cast<uint16_t*>(sc.Hid);
+  bool normed = false;  // sc.O holds the split rows of the layer's normed input
   for (size_t l = 0; l < layers.size(); ++l) {
     const BlockW& w = layers[l];
     char* kc = reinterpret_cast<char*>(kv.k) + l * kv.layer_stride * s.es;
@@ -777,7 +783,7 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
     const bool planes = planes_ok(h, qkv) && planes_ok(h, o) && planes_ok(h, gu) && planes_ok(h, dn);
 
     if (planes) {
-      OTHER(h, launch_split_rows, X, w.attn_norm, h->cfg.rms_eps, so, s.d, M, st);
+      if (!normed) OTHER(h, launch_split_rows, X, w.attn_norm, h->cfg.rms_eps, so, s.d, M, st);
       RCK(run_planes(h, qkv, so, nullptr, sc, st));
     } else {
       RCK(run_linear(h, qkv, sc, st));
@@ -793,14 +799,18 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
       TIMED(h, MBP_KCLASS_ATTN, abytes, launch_attn_decode, a, h->cfg.kv_dtype, max_kv, sc.part, sc.part_floats, st);
     }
 
-    RCK(planes ? run_planes(h, o, so, nullptr, sc, st) : run_linear(h, o, sc, st));
     if (planes) {
-      OTHER(h, launch_split_rows, X, w.ffn_norm, h->cfg.rms_eps, so, s.d, M, st);
+      RCK(run_planes(h, o, so, nullptr, sc, st, so, w.ffn_norm, &normed));
+      if (!normed) OTHER(h, launch_split_rows, X, w.ffn_norm, h->cfg.rms_eps, so, s.d, M, st);
       RCK(run_planes(h, gu, so, sh, sc, st));
+      const bool more = l + 1 < layers.size();
+      RCK(run_planes(h, dn, sh, nullptr, sc, st, more ? so : nullptr, more ? layers[l + 1].attn_norm : nullptr, &normed));
     } else {
+      RCK(run_linear(h, o, sc, st));
       RCK(run_linear(h, gu, sc, st));
+      RCK(run_linear(h, dn, sc, st));
+      normed = false;
     }
-    RCK(planes ? run_planes(h, dn, sh, nullptr, sc, st) : run_linear(h, dn, sc, st));
   }
   return MBP_OK;
 }
