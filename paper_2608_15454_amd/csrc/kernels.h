@@ -103,23 +103,33 @@ struct Ev {
 hipError_t launch_linear(const Linear& L, int wdt, float* inv_rms_scratch, hipStream_t st, const Ev& ev = Ev());
 // A linear layer on split rows: a row of K values as K / 32 groups of 64 bfloat16, the
 // group's 32 hi = bf16(x), then its 32 lo = bf16(x - hi) (4 K bytes, as in float32).  x
-// holds M such rows of ldx values (RMSNorm and gain already applied).  epi as Linear's,
-// except that SWIGLU writes split rows of ldy values to y.
+// holds M such rows of ldx values; the row scales rs (M floats, or nullptr: 1) multiply
+// the products, so an RMSNorm's rows are split as x * gain: embedding rows and gains of 8
+// significant bits stay exact.  epi as Linear's, except that SWIGLU writes split rows of
+// ldy values to y.
 struct PlaneLinear {
+  // what the kernel needs before its first load comes first (two 64-byte lines)
   const uint16_t* x;
+  const float* rs;
   int32_t ldx, M, K, N;
-  Mats mats;
   int32_t kind;
-  Epi epi;
+  // set by launch_planes_at: K splits, whether rs is set, the grid's column blocks, and its
+  // order (log2 of the L2 group's row blocks and the reciprocal of a group's blocks; 0:
+  // plain order)
+  int32_t ksplit, scaled, cb, grl;
+  uint32_t ginv;
+  Mats mats;
   uint16_t* y;
   int32_t ldy;
   float* part;  // split-K scratch (kGemmPartFloats floats)
+  Epi epi;
   // RESID: when next is set and K is split, the kernel that adds the parts also writes
-  // the split rows of RMSNorm(Y) * next_gain (rows of N = ldy values), the next linear's
-  // input (planes_plan tells whether K is split)
+  // the next linear's input, the split rows of Y * next_gain (rows of N = ldy values) and
+  // their scales 1 / RMS(Y) (planes_fuses_norm)
   uint16_t* next;
   const float* next_gain;
   float eps;
+  float* next_rs;
 };
 // Whether a linear of this shape (bfloat16 weights) runs on split rows; n_mat: rows of
 // one matrix of a fused weight (N otherwise).
@@ -136,9 +146,9 @@ hipError_t launch_planes_at(const PlaneLinear& P, PlanesPlan plan, hipStream_t s
 // The sums of ks partial products in L.part and the epilogue (the second half of a
 // split-K launch: only ev.stop is stamped).
 hipError_t launch_gemm_finish(const Linear& L, int ks, hipStream_t st, const Ev& ev);
-// Split rows of M rows of d floats: x, or RMSNorm(x) * gain when gain is set.
-hipError_t launch_split_rows(const float* x, const float* gain, float eps, uint16_t* y, int d, int M, hipStream_t st,
-                             const Ev& ev = Ev());
+// Split rows of M rows of d floats: x, or x * gain with rs = 1 / RMS(x) when gain is set.
+hipError_t launch_split_rows(const float* x, const float* gain, float eps, uint16_t* y, float* rs, int d, int M,
+                             hipStream_t st, const Ev& ev = Ev());
 // Whether launch_linear takes the weight-streaming GEMV path for L.
 bool linear_is_gemv(const Linear& L, int wdt);
 // Split-KV attention (blocks of four waves over 256-key splits) followed by a merge

@@ -62,28 +62,35 @@ struct PTile {
 using PTile128 = PTile<2, 2, 2, 2>;
 using PTile256 = PTile<4, 2, 2, 4>;
 
-template <int WM, int WN, int TI, int TJ>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinear P, int gr, int ksplit) {
+// EK: what the kernel ends with, compiled in (an EpiKind, or kEpiPart: the raw sums of a K
+// range), since a short launch fetches every line of its code uncached: with one kernel
+// for all kinds the 15 us launches of the LM module took 2 to 3 us longer.  kEpiAny: the
+// kind at run time, for the 256 tile, whose launches are long and whose epilogues spill
+// when compiled alone.
+constexpr int kEpiPart = 4, kEpiAny = -1;
+
+template <int WM, int WN, int TI, int TJ, int EK>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinear P) {
   using T = PTile<WM, WN, TI, TJ>;
   constexpr int BM = T::BM, BN = T::BN, GA = T::GA, GB = T::GB;
   __shared__ __attribute__((aligned(1024))) char lds[T::kLds];
+  const int kind = EK == kEpiAny ? P.kind : EK;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // The start is kept short (no division, two lines of arguments): a launch of the LM
+  // module over a prompt lasts 15 us, and its instructions and arguments start uncached.
   int bx = blockIdx.x, by = blockIdx.y;
-  {
-    const int rb = gridDim.y, cb = gridDim.x;
-    if (ksplit == 1 && rb % (8 * gr) == 0) {
-      const int bid = blockIdx.y * cb + blockIdx.x, xcd = bid & 7, l = bid >> 3;
-      const int g = l / (gr * cb), rem = l - g * gr * cb;
-      bx = rem / gr;
-      by = xcd + 8 * (g * gr + rem % gr);
-    }
+  if (P.ginv != 0) {  // XCD k takes groups of 2^grl row blocks k, k + 8, ..., walked rows fastest
+    const int bid = by * P.cb + bx, xcd = bid & 7, l = bid >> 3;
+    const int g = (int)__umulhi((uint32_t)l, P.ginv), rem = l - ((g * P.cb) << P.grl);
+    bx = rem >> P.grl;
+    by = xcd + 8 * ((g << P.grl) + (rem & ((1 << P.grl) - 1)));
   }
   const int m0 = by * BM, n0 = bx * BN;
   const int K = P.K, M = P.M;
   // this block's steps: K / ksplit columns from z K / ksplit on; nk is even and >= 4
-  const int nk = K / kBK / ksplit;
-  const uint32_t kz = blockIdx.z * (uint32_t)nk;
+  const int nk = EK == kEpiPart ? K / kBK / P.ksplit : K / kBK;
+  const uint32_t kz = EK == kEpiPart ? blockIdx.z * (uint32_t)nk : 0;
   // Piece p of a slot is rows 8 p .. 8 p + 7, eight lanes per row of 128 bytes (a load
   // that covers whole lines moves about three times the bytes of one that takes 64 from
   // each).  A row's 16-byte chunks are stored XOR-ed with (row / 2) % 8, so that the
@@ -96,32 +103,25 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
     const int r = (wave * GA + g) * 8 + (lane >> 3);
     va[g] = (uint32_t)min(r, M - 1 - m0) * ldxb + (((lane & 7) ^ ((r >> 1) & 7)) * 16);  // rows past M repeat the last one, never stored
   }
-  const bool pair = P.kind == EPI_SWIGLU || P.kind == EPI_QKV;
+  const bool pair = kind == EPI_SWIGLU || kind == EPI_QKV || (kind == kEpiPart && P.kind == EPI_QKV);
+  // 8 tile columns c .. c + 7 lie in one half of one wave's 32 TJ columns; pair epilogues
+  // keep the even columns in the first half and their odd partners in the second, so a
+  // lane holds both values of its pairs.  wbase: the matrix (of the tile, or of the half)
+  // and its first row; step: rows between columns.
+  const bool gu = kind == EPI_SWIGLU;
+  const int which = kind == EPI_QKV || (kind == kEpiPart && P.mats.mode == MAT_QKV) ? (n0 >= P.mats.rows) + (n0 >= 2 * P.mats.rows) : 0;  // a tile lies in one of q, k, v
+  const char* const wm0 = reinterpret_cast<const char*>(which == 0 ? P.mats.m[0] : which == 1 ? P.mats.m[1] : P.mats.m[2]);
+  const char* const wm1 = reinterpret_cast<const char*>(gu ? P.mats.m[1] : wm0);
+  const int nrow = gu ? n0 >> 1 : n0 - which * P.mats.rows;
+  const uint32_t vrow = (uint32_t)(lane >> 3) * (uint32_t)(pair && !gu ? 2 : 1) * (uint32_t)K * 2;
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
-    // 8 tile columns c .. c + 7 lie in one half of one wave's 32 TJ columns; pair
-    // epilogues keep the even columns in the first half and their odd partners in the
-    // second, so a lane holds both values of its pairs
-    const int c = (wave * GB + g) * 8;
-    int n = n0 + c, step = 1;
-    if (pair) {
-      const int cc = c % (32 * TJ);
-      n = n0 + (c - cc) + 2 * (cc % (16 * TJ)) + cc / (16 * TJ);
-      step = 2;
-    }
-    int which = 0, r = n;
-    if (P.mats.mode == MAT_QKV) {
-      which = n / P.mats.rows;
-      r = n - which * P.mats.rows;
-    } else if (P.mats.mode == MAT_GATEUP) {
-      which = n & 1;
-      r = n >> 1;
-      step = 1;
-    }
-    const void* base = which == 0 ? P.mats.m[0] : (which == 1 ? P.mats.m[1] : P.mats.m[2]);
-    sb[g] = reinterpret_cast<const char*>(base) + ((size_t)r * K + kz * 32) * 2;
-    vb[g] = (uint32_t)((lane >> 3) * step) * (uint32_t)K * 2 + (((lane & 7) ^ (((c + (lane >> 3)) >> 1) & 7)) * 16);
+    const int c = (wave * GB + g) * 8, cc = c % (32 * TJ), odd = cc / (16 * TJ), in = cc % (16 * TJ), wc = c / (32 * TJ);
+    const int r = !pair ? nrow + c : gu ? nrow + wc * 16 * TJ + in : nrow + wc * 32 * TJ + 2 * in + odd;
+    sb[g] = (pair && odd ? wm1 : wm0) + ((size_t)r * K + kz * 32) * 2;
+    vb[g] = vrow + (((lane & 7) ^ (((c + (lane >> 3)) >> 1) & 7)) * 16);
   }
+  const int wm = wave / WN, wn = wave % WN;
   const char* sx = reinterpret_cast<const char*>(P.x) + (size_t)m0 * ldxb + kz * 128;
   const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   // piece g of step k's X into the slot at buf, of weight step j (two steps) into slot j % 2
@@ -133,7 +133,6 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
     dma16(lbase + 3 * T::kA + (uint32_t)(j & 1) * T::kW + (uint32_t)(wave * GB + g) * 1024, vb[g],
           sb[g] + (size_t)min(j, nk / 2 - 1) * 128);
   };
-  const int wm = wave / WN, wn = wave % WN;
   f32x16 acc[TI][TJ];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
@@ -188,6 +187,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
 #pragma unroll
   for (int g = 0; g < GA; ++g) req_a(g, 2, 2 * T::kA);
   asm volatile("s_waitcnt vmcnt(12)\n\ts_barrier" ::"s"(lbase) : "memory");
+  // lane l holds the scale of row l of the wave's 64 (bytes of x, unused, when not scaled);
+  // one more load in flight only makes the first step's wait stricter
+  static_assert(TI == 2, "64 rows per wave");
+  const float rsl = kind != EPI_RESID ? P.rs[min(m0 + wm * 64 + lane, M - 1)] : 0.f;
   Frag f0, f1;
   uint32_t a0 = 0, a1 = T::kA, a2 = 2 * T::kA;  // slots of steps k, k + 1, k + 2
 #pragma unroll
@@ -217,11 +220,25 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
     w = T::kW - w;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land after the block has ended
-  const int jj = lane & 31, half = lane >> 5;
+  // The epilogue's row and column numbers start here: computed from the same values as the
+  // loop's, the compiler would move them above the loop and spill.
+  int em = m0 + wm * 32 * TI, en = n0, el = lane, ew = wn, ec = nrow;
+  asm volatile("" : "+s"(em), "+s"(en), "+v"(el), "+s"(ew), "+s"(ec));
+  const int jj = el & 31, half = el >> 5;
   const bool full = m0 + BM <= M;
-  auto row_of = [&](int i, int r) { return m0 + wm * 32 * TI + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3); };
-  if (ksplit > 1) {
-    // raw sums of this K range, columns in the matrix's order: gemm_finish_kernel adds
+  auto row_of = [&](int i, int r) { return em + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3); };
+  if (kind != EPI_RESID && P.scaled) {
+    static_for<TI>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float sc = __shfl(rsl, i * 32 + 8 * (r >> 2) + 4 * half + (r & 3));
+        static_for<TJ>([&](auto jc) __attribute__((always_inline)) { acc[i][decltype(jc)::value][r] *= sc; });
+      }
+    });
+  }
+  if (kind == kEpiPart) {
+    // sums of this K range, columns in the matrix's order: gemm_finish_kernel adds
     // the ranges and runs the epilogue
     float* part = P.part + (size_t)blockIdx.z * M * P.N;
     static_for<TI>([&](auto ic) __attribute__((always_inline)) {
@@ -230,7 +247,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
       for (int r = 0; r < 16; ++r) {
         const int m = row_of(i, r);
         if (full || m < M) {
-          float* y = part + (size_t)m * P.N + n0 + wn * 32 * TJ;
+          float* y = part + (size_t)m * P.N + en + ew * 32 * TJ;
           if (pair) {
             static_for<TJ / 2>([&](auto jc) __attribute__((always_inline)) {
               constexpr int j = decltype(jc)::value;
@@ -245,9 +262,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
         }
       }
     });
-    return;
-  }
-  if (P.kind == EPI_SWIGLU) {
+  } else if (kind == EPI_SWIGLU) {
     // silu(gate) * up as planes; neighbouring lanes trade values so that each stores two
     // columns of one row as one word: the even lane row r, the odd one row r + 1
     const size_t ldy = (size_t)P.ldy * 2;
@@ -265,7 +280,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
           uint32_t hi, lo;
           bf16_hi_lo2(c0, c1, hi, lo);
           // 32 columns' group of the split row: hi halves, then lo
-          uint16_t* y = P.y + (size_t)m * ldy + 2 * ((n0 >> 1) + wn * 16 * TJ + j * 32) + (jj & ~1);
+          uint16_t* y = P.y + (size_t)m * ldy + 2 * ((en >> 1) + ew * 16 * TJ + j * 32) + (jj & ~1);
           if (full || m < M) {
             *reinterpret_cast<uint32_t*>(y) = hi;
             *reinterpret_cast<uint32_t*>(y + 32) = lo;
@@ -273,9 +288,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
         });
       }
     });
-  } else if (P.kind == EPI_QKV) {
+  } else if (kind == EPI_QKV) {
     const Epi e = P.epi;
-    const int which = n0 / e.d, col0 = n0 - which * e.d + wn * 32 * TJ;  // a tile lies in one of q, k, v
+    const int col0 = ec + ew * 32 * TJ;
     static_for<TI>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
 #pragma unroll
@@ -319,13 +334,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
   } else {
     float* const Y = P.epi.Y;
     const size_t ldy = (size_t)P.epi.ldy;
-    const bool add = P.kind == EPI_RESID;
+    const bool add = kind == EPI_RESID;
     static_for<TI>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int m = row_of(i, r);
-        float* y = Y + (size_t)m * ldy + n0 + wn * 32 * TJ + jj;
+        float* y = Y + (size_t)m * ldy + en + ew * 32 * TJ + jj;
         if (full || m < M) {
           float old[TJ];
 #pragma unroll
@@ -340,20 +355,20 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
   }
 }
 
-// Split rows of float32 rows: x, or RMSNorm(x) * gain; a wave per row.  Eight lanes read
+// Split rows of float32 rows: x, or x * gain and rs = 1 / RMS(x); a wave per row.  Eight lanes read
 // a group's 128 bytes in one load and write them back as its halves, so y may be x.
 // V > 0: rows of d = 256 V values, kept in registers between the norm and the split.
 template <int V>
-__global__ __launch_bounds__(256) void split_rows_kernel(const float* x, const float* gain, float eps, uint16_t* y, int d,
-                                                         int M) {
+__global__ __launch_bounds__(256) void split_rows_kernel(const float* x, const float* gain, float eps, uint16_t* y, float* rs,
+                                                         int d, int M) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= M) return;
   const float* xr = x + (size_t)row * d;
   uint16_t* yr = y + (size_t)row * 2 * d;
-  auto put = [&](float4 t, float sc, int k) {
+  auto put = [&](float4 t, int k) {
     if (gain != nullptr) {
       const float4 g = *reinterpret_cast<const float4*>(gain + k);
-      t.x *= sc * g.x; t.y *= sc * g.y; t.z *= sc * g.z; t.w *= sc * g.w;
+      t.x *= g.x; t.y *= g.y; t.z *= g.z; t.w *= g.w;
     }
     uint32_t h0, l0, h1, l1;
     bf16_hi_lo2(t.x, t.y, h0, l0);
@@ -369,77 +384,93 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* x, const f
 #pragma unroll
     for (int i = 0; i < V; ++i) v[i] = *reinterpret_cast<const float4*>(xr + i * 256 + lane * 4);
 #pragma unroll
-    for (int i = 0; i < V; ++i) ss += sq(v[i]);
-    const float sc = gain != nullptr ? 1.0f / sqrtf(wave_sum(ss) / (float)d + eps) : 1.f;
-#pragma unroll
-    for (int i = 0; i < V; ++i) put(v[i], sc, i * 256 + lane * 4);
-  } else {
-    float sc = 1.f;
-    if (gain != nullptr) {
-      for (int k = lane * 4; k < d; k += 256) ss += sq(*reinterpret_cast<const float4*>(xr + k));
-      sc = 1.0f / sqrtf(wave_sum(ss) / (float)d + eps);
+    for (int i = 0; i < V; ++i) {
+      ss += sq(v[i]);
+      put(v[i], i * 256 + lane * 4);
     }
-    for (int k = lane * 4; k < d; k += 256) put(*reinterpret_cast<const float4*>(xr + k), sc, k);
+  } else {
+    for (int k = lane * 4; k < d; k += 256) {
+      const float4 t = *reinterpret_cast<const float4*>(xr + k);
+      ss += sq(t);
+      put(t, k);
+    }
+  }
+  if (gain != nullptr) {
+    ss = wave_sum(ss);
+    if (lane == 0) rs[row] = 1.0f / sqrtf(ss / (float)d + eps);
   }
 }
 
-// The second half of a split-K product onto the residual rows and the norm before the
+// The second half of a split-K product onto the residual rows and the split before the
 // next linear in one pass: row m of x gets the sum of its ks partial rows (added in order
-// z = 0, 1, ..., then to x, as gemm_finish_kernel does), and y the split row of
-// RMSNorm(x) * gain.  A block per row; bound by its launch and one round of loads (at
-// 531 rows the two kernels it replaces took 5.5 + 5.4 us).  V: 1024 V >= d.
-template <int V>
+// z = 0, 1, ..., then to x, as gemm_finish_kernel does), y the split row of x * gain and
+// rs its 1 / RMS.  A block per row; bound by its launch and one round of loads (at
+// 531 rows the two kernels it replaces took 5.5 + 5.4 us).
 __global__ __launch_bounds__(256) void finish_split_kernel(const float* part, int ks, int M, int d, float* x, const float* gain,
-                                                           float eps, uint16_t* y) {
+                                                           float eps, uint16_t* y, float* rs) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   const size_t zs = (size_t)M * d;
-  float4 v[V], g[V];
   float ss = 0.f;
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int k = (i * 256 + tid) * 4;
-    v[i] = g[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (k < d) {
-      const float4 old = *reinterpret_cast<const float4*>(x + (size_t)row * d + k);
-      g[i] = *reinterpret_cast<const float4*>(gain + k);
-      const float* pp = part + (size_t)row * d + k;
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k = tid * 4; k < d; k += 1024) {
+    const float4 old = *reinterpret_cast<const float4*>(x + (size_t)row * d + k);
+    const float4 g = *reinterpret_cast<const float4*>(gain + k);
+    const float* pp = part + (size_t)row * d + k;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-      for (int z = 0; z < ks; ++z) {
-        const float4 t = *reinterpret_cast<const float4*>(pp + z * zs);
-        a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
-      }
-      a.x += old.x; a.y += old.y; a.z += old.z; a.w += old.w;
-      *reinterpret_cast<float4*>(x + (size_t)row * d + k) = a;
-      ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
-      v[i] = a;
+    for (int z = 0; z < ks; ++z) {
+      const float4 t = *reinterpret_cast<const float4*>(pp + z * zs);
+      a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
     }
-  }
-  ss = wave_sum(ss);
-  if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
-  const float sc = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int k = (i * 256 + tid) * 4;
-    if (k >= d) continue;
+    a.x += old.x; a.y += old.y; a.z += old.z; a.w += old.w;
+    *reinterpret_cast<float4*>(x + (size_t)row * d + k) = a;
+    ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
     uint32_t h0, l0, h1, l1;
-    bf16_hi_lo2(v[i].x * (sc * g[i].x), v[i].y * (sc * g[i].y), h0, l0);
-    bf16_hi_lo2(v[i].z * (sc * g[i].z), v[i].w * (sc * g[i].w), h1, l1);
+    bf16_hi_lo2(a.x * g.x, a.y * g.y, h0, l0);
+    bf16_hi_lo2(a.z * g.z, a.w * g.w, h1, l1);
     uint16_t* o = y + (size_t)row * 2 * d + 2 * (k & ~31) + (k & 31);
     *reinterpret_cast<uint2*>(o) = make_uint2(h0, h1);
     *reinterpret_cast<uint2*>(o + 32) = make_uint2(l0, l1);
   }
+  ss = wave_sum(ss);
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
+  __syncthreads();
+  if (tid == 0) rs[row] = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
 }
 
 template <int WM, int WN, int TI, int TJ>
 hipError_t planes_launch_t(PTile<WM, WN, TI, TJ>, const PlaneLinear& P, int ks, hipStream_t st, const Ev& ev) {
   using T = PTile<WM, WN, TI, TJ>;
-  // row blocks per L2 group: about 2 MiB of activation rows
-  const int gr = std::max(1, std::min(8, (int)((2 << 20) / ((int64_t)T::BM * P.K * 4))));
-  return plaunch(gemm_planes_kernel<WM, WN, TI, TJ>, dim3(P.N / T::BN, (P.M + T::BM - 1) / T::BM, ks), dim3(64 * T::NW),
-                 st, ev.start, ks > 1 ? nullptr : ev.stop, P, gr, ks);
+  PlaneLinear Q = P;
+  Q.ksplit = ks;
+  Q.scaled = P.rs != nullptr;
+  if (!Q.scaled) Q.rs = reinterpret_cast<const float*>(P.x);  // M readable floats
+  Q.cb = P.N / T::BN;
+  const int rb = (P.M + T::BM - 1) / T::BM;
+  // row blocks per L2 group: about 2 MiB of activation rows, a power of two; the kernel
+  // divides block numbers below 2^16 by the group's blocks with a rounded-up reciprocal
+  int grl = 0;
+  while (grl < 3 && ((int64_t)T::BM * P.K * 4 << (grl + 1)) <= (2 << 20)) ++grl;
+  const int64_t group = (int64_t)Q.cb << grl;
+  Q.grl = grl;
+  Q.ginv = 0;
+  if (ks == 1 && rb % (8 << grl) == 0 && group > 1 && (int64_t)rb * Q.cb / 8 * group < ((int64_t)1 << 32))
+    Q.ginv = (uint32_t)((((uint64_t)1 << 32) + group - 1) / group);
+  auto go = [&](auto kern) {
+    return plaunch(kern, dim3(Q.cb, rb, ks), dim3(64 * T::NW), st, ev.start, ks > 1 ? nullptr : ev.stop, Q);
+  };
+  if constexpr (T::NW == 8) {
+    if (ks > 1) return hipErrorInvalidValue;  // the 256 tile is not split
+    return go(gemm_planes_kernel<WM, WN, TI, TJ, kEpiAny>);
+  } else {
+    if (ks > 1) return go(gemm_planes_kernel<WM, WN, TI, TJ, kEpiPart>);
+    switch (P.kind) {
+      case EPI_SWIGLU: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_SWIGLU>);
+      case EPI_QKV: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_QKV>);
+      case EPI_RESID: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_RESID>);
+      default: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_STORE>);
+    }
+  }
 }
 
 }  // namespace
@@ -472,20 +503,16 @@ PlanesPlan planes_plan(const PlaneLinear& P) {
   return {128, ks};
 }
 
-static bool fuse_shape(const PlaneLinear& P) { return P.kind == EPI_RESID && P.epi.ldy == P.N && P.N <= 4096; }
+static bool fuse_shape(const PlaneLinear& P) { return P.kind == EPI_RESID && P.epi.ldy == P.N; }
 
 bool planes_fuses_norm(const PlaneLinear& P) { return fuse_shape(P) && planes_plan(P).ks > 1; }
 
 hipError_t launch_planes_at(const PlaneLinear& P, PlanesPlan plan, hipStream_t st, const Ev& ev) {
   const hipError_t e = plan.tile == 256 ? planes_launch_t(PTile256{}, P, plan.ks, st, ev) : planes_launch_t(PTile128{}, P, plan.ks, st, ev);
   if (e != hipSuccess || plan.ks == 1) return e;
-  if (P.next != nullptr && fuse_shape(P)) {
-    auto go = [&](auto kern) {
-      return plaunch(kern, dim3(P.M), dim3(256), st, nullptr, ev.stop, (const float*)P.part, plan.ks, P.M, P.N, P.epi.Y,
-                     P.next_gain, P.eps, P.next);
-    };
-    return P.N <= 1024 ? go(finish_split_kernel<1>) : P.N <= 2048 ? go(finish_split_kernel<2>) : go(finish_split_kernel<4>);
-  }
+  if (P.next != nullptr && fuse_shape(P))
+    return plaunch(finish_split_kernel, dim3(P.M), dim3(256), st, nullptr, ev.stop, (const float*)P.part, plan.ks, P.M, P.N,
+                   P.epi.Y, P.next_gain, P.eps, P.next, P.next_rs);
   Linear L{};
   L.M = P.M; L.K = P.K; L.N = P.N; L.epi = P.epi; L.epi.kind = P.kind; L.part = P.part;
   return launch_gemm_finish(L, plan.ks, st, ev);
@@ -496,11 +523,11 @@ hipError_t launch_planes(const PlaneLinear& P, hipStream_t st, const Ev& ev) {
   return launch_planes_at(P, planes_plan(P), st, ev);
 }
 
-hipError_t launch_split_rows(const float* x, const float* gain, float eps, uint16_t* y, int d, int M, hipStream_t st,
-                             const Ev& ev) {
+hipError_t launch_split_rows(const float* x, const float* gain, float eps, uint16_t* y, float* rs, int d, int M,
+                             hipStream_t st, const Ev& ev) {
   if (M <= 0) return hipSuccess;
   const dim3 grid((M + 3) / 4);
-  auto go = [&](auto kern) { return plaunch(kern, grid, dim3(256), st, ev.start, ev.stop, x, gain, eps, y, d, M); };
+  auto go = [&](auto kern) { return plaunch(kern, grid, dim3(256), st, ev.start, ev.stop, x, gain, eps, y, rs, d, M); };
   if (d == 1024) return go(split_rows_kernel<4>);
   if (d == 2048) return go(split_rows_kernel<8>);
   return go(split_rows_kernel<0>);

@@ -553,15 +553,15 @@ double linear_bytes(const mbp_handle* h, const Linear& L) {
   return N * K * wb + M * K * 4 + out;
 }
 
-// L on split input rows x (L.X and L.gain are not read); y: where a SwiGLU's rows go.
-// With next (a residual product): *fused tells whether the split rows of the result's
-// RMSNorm with next_gain were written there too.
+// L on split input rows x (L.X is not read; with a gain, their scales are in sc.inv); y:
+// where a SwiGLU's rows go.  With next (a residual product): *fused tells whether the split
+// rows of the result times next_gain were written there, and their scales to sc.inv.
 int run_planes(mbp_handle* h, const Linear& L, const uint16_t* x, uint16_t* y, const Scratch& sc, hipStream_t st,
                uint16_t* next = nullptr, const float* next_gain = nullptr, bool* fused = nullptr) {
   PlaneLinear P{};
-  P.x = x; P.ldx = L.ldx; P.M = L.M; P.K = L.K; P.N = L.N; P.mats = L.mats; P.kind = L.epi.kind; P.epi = L.epi;
+  P.x = x; P.rs = L.gain != nullptr ? sc.inv : nullptr; P.ldx = L.ldx; P.M = L.M; P.K = L.K; P.N = L.N; P.mats = L.mats; P.kind = L.epi.kind; P.epi = L.epi;
   P.y = y; P.ldy = L.epi.ldy; P.part = sc.gpart;
-  P.next = next; P.next_gain = next_gain; P.eps = h->cfg.rms_eps;
+  P.next = next; P.next_gain = next_gain; P.eps = h->cfg.rms_eps; P.next_rs = sc.inv;
   if (fused != nullptr) *fused = next != nullptr && planes_fuses_norm(P);
   TIMED(h, MBP_KCLASS_GEMM, linear_bytes(h, L), launch_planes, P, st);
   return MBP_OK;
@@ -583,7 +583,7 @@ int run_linear(mbp_handle* h, Linear L, const Scratch& sc, hipStream_t st) {
   if (L.M >= kSplitFirstRows && L.epi.kind == EPI_STORE && L.xidx == nullptr && L.gain2 == nullptr && L.K == h->sz.d &&
       L.ldx == L.K && planes_ok(h, L)) {
     uint16_t* so = reinterpret_cast<uint16_t*>(sc.O);
-    OTHER(h, launch_split_rows, L.X, L.gain, L.eps, so, L.K, L.M, st);
+    OTHER(h, launch_split_rows, L.X, L.gain, L.eps, so, sc.inv, L.K, L.M, st);
     return run_planes(h, L, so, nullptr, sc, st);
   }
   L.part = sc.gpart;
@@ -783,7 +783,7 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
     const bool planes = planes_ok(h, qkv) && planes_ok(h, o) && planes_ok(h, gu) && planes_ok(h, dn);
 
     if (planes) {
-      if (!normed) OTHER(h, launch_split_rows, X, w.attn_norm, h->cfg.rms_eps, so, s.d, M, st);
+      if (!normed) OTHER(h, launch_split_rows, X, w.attn_norm, h->cfg.rms_eps, so, sc.inv, s.d, M, st);
       RCK(run_planes(h, qkv, so, nullptr, sc, st));
     } else {
       RCK(run_linear(h, qkv, sc, st));
@@ -801,7 +801,7 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
 
     if (planes) {
       RCK(run_planes(h, o, so, nullptr, sc, st, so, w.ffn_norm, &normed));
-      if (!normed) OTHER(h, launch_split_rows, X, w.ffn_norm, h->cfg.rms_eps, so, s.d, M, st);
+      if (!normed) OTHER(h, launch_split_rows, X, w.ffn_norm, h->cfg.rms_eps, so, sc.inv, s.d, M, st);
       RCK(run_planes(h, gu, so, sh, sc, st));
       const bool more = l + 1 < layers.size();
       RCK(run_planes(h, dn, sh, nullptr, sc, st, more ? so : nullptr, more ? layers[l + 1].attn_norm : nullptr, &normed));
@@ -1333,7 +1333,7 @@ int draft(mbp_handle* h, int n, float tau, bool threshold, uint8_t* d_cand, floa
       if (planes_ok(h, gu) && planes_ok(h, dn)) {
         uint16_t* so = reinterpret_cast<uint16_t*>(sc.O);
         uint16_t* sh = reinterpret_cast<uint16_t*>(sc.Hid);
-        OTHER(h, launch_split_rows, h1, w.norm, c.rms_eps, so, s.d, B, h->st);
+        OTHER(h, launch_split_rows, h1, w.norm, c.rms_eps, so, sc.inv, s.d, B, h->st);
         RCK(run_planes(h, gu, so, sh, sc, h->st));
         RCK(run_planes(h, dn, sh, nullptr, sc, h->st));
       } else {
