@@ -232,7 +232,7 @@ __device__ __forceinline__ const W* mat_row(const Mats& mt, int n, int K) {
   if (mt.mode == MAT_SINGLE) {
     which = 0; r = n;
   } else if (mt.mode == MAT_QKV) {
-    which = n / mt.rows; r = n - which * mt.rows;
+    which = (n >= mt.rows) + (n >= 2 * mt.rows); r = n - which * mt.rows;
   } else {
     which = n & 1; r = n >> 1;
   }

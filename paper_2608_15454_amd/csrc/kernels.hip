@@ -49,8 +49,8 @@ __device__ __forceinline__ void epi_pair(const Epi& e, int i, int n, float a0, f
     return;
   }
   const int d = e.d;
-  const int which = n / d, c = n - which * d;
-  const int h = c / e.dh, ee = c - h * e.dh;
+  const int which = (n >= d) + (n >= 2 * d), c = n - which * d;
+  const int h = e.dh == 64 ? c >> 6 : c >> 5, ee = c & (e.dh - 1);  // head sizes are 32 and 64
   if (which < 2) {  // rotate q and k: pair (ee, ee+1) by position * theta_{ee/2}
     const float2 cs = e.rope[(size_t)e.tok.pos[i] * (e.dh >> 1) + (ee >> 1)];
     const float r0 = a0 * cs.x - a1 * cs.y;
@@ -454,41 +454,41 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(Linear L, int ksplit) {
   }
 }
 
-// Sum of the ksplit partials of gemm_mfma_kernel and the epilogue, one thread per
-// output (or output pair for SwiGLU / QKV).
+// Sum of the ksplit partials of gemm_mfma_kernel and the epilogue: four columns of one row
+// per thread, a row per blockIdx.y (no division, one round of 16-byte loads; the launch
+// itself is most of its time).
 __global__ __launch_bounds__(256) void gemm_finish_kernel(Linear L, int ksplit) {
   const bool pair = L.epi.kind == EPI_SWIGLU || L.epi.kind == EPI_QKV;
-  const int per_row = pair ? L.N / 2 : L.N;
-  const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)L.M * per_row) return;
-  const int m = (int)(idx / per_row);
-  const int n = (int)(idx - (int64_t)m * per_row) * (pair ? 2 : 1);
-  // The splits are added in order z = 0, 1, ...; the unrolled loops only issue several
-  // splits' loads before the first add (a pair is one 8-byte load: n and N are even).
-  float a0 = 0.f, a1 = 0.f;
+  const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (n >= L.N) return;
+  // The splits are added in order z = 0, 1, ...; the unrolled loop only issues several
+  // splits' loads before the first add (N is a multiple of 64).
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
   const float* pp = L.part + (size_t)m * L.N + n;
   const size_t zs = (size_t)L.M * L.N;
-  if (pair) {
 #pragma unroll 8
-    for (int z = 0; z < ksplit; ++z) {
-      const float2 t = *reinterpret_cast<const float2*>(pp + z * zs);
-      a0 += t.x;
-      a1 += t.y;
-    }
-  } else {
-#pragma unroll 8
-    for (int z = 0; z < ksplit; ++z) a0 += pp[z * zs];
+  for (int z = 0; z < ksplit; ++z) {
+    const float4 t = *reinterpret_cast<const float4*>(pp + z * zs);
+    a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
   }
   if (L.gain != nullptr) {  // RMSNorm: 1/RMS of the row from the splits' sums of squares
     float ss = 0.f;
 #pragma unroll 8
     for (int z = 0; z < ksplit; ++z) ss += L.part[(size_t)ksplit * L.M * L.N + (size_t)z * L.M + m];
     const float sc = 1.0f / sqrtf(ss / (float)L.K + L.eps);
-    a0 *= sc;
-    a1 *= sc;
+    a.x *= sc; a.y *= sc; a.z *= sc; a.w *= sc;
   }
-  if (pair) epi_pair(L.epi, m, n, a0, a1);
-  else epi_single(L.epi, m, n, a0);
+  if (pair) {
+    epi_pair(L.epi, m, n, a.x, a.y);
+    epi_pair(L.epi, m, n + 2, a.z, a.w);
+    return;
+  }
+  float4* y = reinterpret_cast<float4*>(L.epi.Y + (size_t)m * L.epi.ldy + n);
+  if (L.epi.kind == EPI_RESID) {
+    const float4 o = *y;
+    a.x += o.x; a.y += o.y; a.z += o.z; a.w += o.w;
+  }
+  *y = a;
 }
 
 // Linears of 17..64 rows with bfloat16 weights and K = 8 x 32 x NSTEP (decode passes
@@ -2132,9 +2132,7 @@ hipError_t attn_prefill_t(const Attn& a, const int32_t* tiles, int ntiles, hipSt
 }  // namespace
 
 hipError_t launch_gemm_finish(const Linear& L, int ks, hipStream_t st, const Ev& ev) {
-  const bool pair = L.epi.kind == EPI_SWIGLU || L.epi.kind == EPI_QKV;
-  const int64_t items = (int64_t)L.M * (pair ? L.N / 2 : L.N);
-  return klaunch(gemm_finish_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, nullptr, ev.stop, L, ks);
+  return klaunch(gemm_finish_kernel, dim3((L.N / 4 + 255) / 256, L.M), dim3(256), 0, st, nullptr, ev.stop, L, ks);
 }
 
 bool linear_is_gemv(const Linear& L, int wdt) {
