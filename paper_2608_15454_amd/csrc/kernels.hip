@@ -975,12 +975,13 @@ __global__ __launch_bounds__(128 * KG, KG == 4 ? 2 : 3) void attn_prefill_mfma_k
   // Q^T fragments (the B operand of S^T): query qi, dims ks*16 + half*8 .. +7
   f16x8 qh[4], ql[4];
   {
+    const float qscale = a.scale * 1.44269504f;  // scores in units of log 2: the softmax takes exp2 of them
     const float* qp = a.Q + (size_t)qrow * a.ldq + h * DH + half * 8;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float v = qp[ks * 16 + j] * a.scale;
+        const float v = qp[ks * 16 + j] * qscale;
         const _Float16 hv = (_Float16)v;
         qh[ks][j] = hv;
         ql[ks][j] = (_Float16)(v - (float)hv);
@@ -1061,37 +1062,45 @@ __global__ __launch_bounds__(128 * KG, KG == 4 ? 2 : 3) void attn_prefill_mfma_k
         s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[ks], s[cb], 0, 0, 0);
       }
     }
+    // Masked keys get -inf; a causal block below all of the wave's queries needs no mask
+    // (all but the last block or two of a tile's chain, whose mask took as many
+    // instructions as its softmax).
+    if (gt != nullptr || k0 + 63 > slot0 + 32 * qw || k0 + 63 >= kvmax) {
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int kk = 32 * cb + 8 * (r >> 2) + 4 * half + (r & 3), jk = k0 + kk;
+          const bool vis = jk < kvmax && jk <= islot && Gs[kk] >= gq - 1;
+          s[cb][r] = vis ? s[cb][r] : -INFINITY;
+        }
+    }
     float mx = -INFINITY;
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int kk = 32 * cb + 8 * (r >> 2) + 4 * half + (r & 3), j = k0 + kk;
-        const bool vis = j < kvmax && j <= islot && Gs[kk] >= gq - 1;
-        s[cb][r] = vis ? s[cb][r] : -INFINITY;
-        mx = fmaxf(mx, s[cb][r]);
-      }
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[cb][r]);
     mx = pair_max<32>(mx);  // the other half of the wave holds the query's other keys
     const float m_new = fmaxf(m_run, mx);
-    const float alpha = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
+    // nothing visible yet: any finite reference gives probabilities of 0
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
     float ls = 0.f;
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float pv = (s[cb][r] == -INFINITY) ? 0.f : __expf(s[cb][r] - m_new);
+        const float pv = __builtin_amdgcn_exp2f(s[cb][r] - m_ref);
         s[cb][r] = pv;
         ls += pv;
       }
     ls = pair_sum<32>(ls);
-    if (m_new != -INFINITY) {
-      l_run = l_run * alpha + ls;
-      m_run = m_new;
+    l_run = l_run * alpha + ls;
+    m_run = m_new;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        o0[r] *= alpha;
-        o1[r] *= alpha;
-      }
+    for (int r = 0; r < 16; ++r) {
+      o0[r] *= alpha;
+      o1[r] *= alpha;
     }
     // O^T += V^T P^T, k steps of 16 keys: step (cb, t) takes registers 8t .. 8t+7 of
     // block cb, i.e. keys 32 cb + 16 t + 4 half + {0..3} and + 8 + {0..3}
@@ -1149,7 +1158,7 @@ __global__ __launch_bounds__(128 * KG, KG == 4 ? 2 : 3) void attn_prefill_mfma_k
       const float mg = w[0];
       if (mg == -INFINITY) continue;  // no visible key in that group's blocks
       const float mn = fmaxf(m_run, mg);
-      const float a0 = (m_run == -INFINITY) ? 0.f : __expf(m_run - mn), a1 = __expf(mg - mn);
+      const float a0 = __builtin_amdgcn_exp2f(m_run - mn), a1 = __builtin_amdgcn_exp2f(mg - mn);
       l_run = l_run * a0 + w[64] * a1;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {

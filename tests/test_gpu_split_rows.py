@@ -27,13 +27,15 @@ def test_forward_row_edges(model, T):
     check(dec, oracle.to_float64(raw), model, synth.make_prompt(T, T), TOL)
 
 
-@pytest.mark.parametrize("kw", [dict(engine=False), dict(kv_dtype=0), dict(kv_dtype=1)])
+@pytest.mark.parametrize("kw", [dict(engine=False), dict(kv_dtype=0), dict(kv_dtype=1), dict(max_chunk=100)])
 def test_forward_cache_types(kw):
     """Float32 and bfloat16 caches take the general prefill attention; bfloat16 keeps 8
-    bits of a key, 8 times the error of float16."""
+    bits of a key, 8 times the error of float16.  Passes of 100 rows: key blocks that lie
+    below, across and above a tile's first query at odd offsets."""
     raw = synth.make_weights(D256, seed=2, gain_jitter=0.3)
-    dec = new_decoder(D256, raw, 1, 200, **kw)
-    check(dec, oracle.to_float64(raw), D256, synth.make_prompt(2, 150), TOL * (8 if kw.get("kv_dtype") == 1 else 1))
+    T = 333 if "max_chunk" in kw else 150
+    dec = new_decoder(D256, raw, 1, T + 50, **kw)
+    check(dec, oracle.to_float64(raw), D256, synth.make_prompt(2, T), TOL * (8 if kw.get("kv_dtype") == 1 else 1))
 
 
 @pytest.mark.parametrize("batch,head", [(65, "lca"), (70, "lca"), (66, "mlp")])
