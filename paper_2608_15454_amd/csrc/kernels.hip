@@ -181,13 +181,9 @@ __global__ __launch_bounds__(256) void gemv_kernel(Linear L) {
         float xv[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; v += XV) {
-          XT t = *reinterpret_cast<const XT*>(xrow[m] + k0 + v);
+          const XT t = live[m] ? *reinterpret_cast<const XT*>(xrow[m] + k0 + v) : XT{};
           xv[v] = t.x; xv[v + 1] = t.y;
           if constexpr (XV == 4) { xv[v + 2] = t.z; xv[v + 3] = t.w; }
-        }
-        if (!live[m]) {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) xv[v] = 0.f;
         }
         if (norm) {
 #pragma unroll
@@ -900,8 +896,14 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(Attn a, const int32_t
     }
   }
   if (r < cnt) {
+    if (!a.split) {  // float32 rows: a plain loop, which becomes 16-byte stores
+      float* op = a.O + (size_t)(t0 + r) * a.ldo + h * DH + cq * OD;
 #pragma unroll
-    for (int od = 0; od < OD; ++od) store_o(a.O, a.ldo, a.split, t0 + r, h * DH + cq * OD + od, o[od] / l_run);
+      for (int od = 0; od < OD; ++od) op[od] = o[od] / l_run;
+      return;
+    }
+#pragma unroll
+    for (int od = 0; od < OD; ++od) store_o(a.O, a.ldo, 1, t0 + r, h * DH + cq * OD + od, o[od] / l_run);
   }
 }
 

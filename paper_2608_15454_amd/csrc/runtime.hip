@@ -682,7 +682,7 @@ bool engine_call(const mbp_handle* h, const EngStack* es, const EIo& io, const T
   if (!h->engine || es == nullptr || es->nops == 0 || tok.M > kEngineMaxRows || grid <= 0) return false;
   if (tok.M > 1 && !engine_multi_row(h->eng_shape)) return false;
   // Short contexts: one block per (row, head) takes all keys (S = 1), which saves the
-  // merge step.  Up to one load round of the block's waves (448 keys) for a single row,
+  // merge step.  Up to one load round of the block's waves (448 keys, 224 in float32) for a single row,
   // two for several, whose merge does more (generation of 2 bytes a step on ~200 latents,
   // batch 1: 10.77 -> 10.61 ms; batch 8 on 130: 24.85 -> 24.10 at 448, 23.65 at 896 with
   // contexts of 900 bytes; batch 1 on ~790 latents: 24.13 ms split, 24.39 in one block,
@@ -690,7 +690,8 @@ bool engine_call(const mbp_handle* h, const EngStack* es, const EIo& io, const T
   const int items_per_split = tok.M * s.H;
   const int cached_splits = std::max(1, grid / items_per_split - 1);
   const int chunk = std::max(64, (max_ns + cached_splits - 1) / cached_splits + 63) / 64 * 64;
-  const int S = max_ns <= (tok.M == 1 ? 448 : 896) ? 1 : (max_ns + chunk - 1) / chunk + 1;
+  const int round = h->cfg.kv_dtype == MBP_F32 ? 224 : 448;
+  const int S = max_ns <= (tok.M == 1 ? round : 2 * round) ? 1 : (max_ns + chunk - 1) / chunk + 1;
   if (S > s.Esplit) return false;
   *c = ECall{};
   c->io = io;

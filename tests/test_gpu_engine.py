@@ -122,11 +122,11 @@ def test_engine_matches_per_kernel_path_d1024():
     assert np.array_equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("batch,length", [(1, 446), (2, 893)])
+@pytest.mark.parametrize("batch,length", [(1, 222), (2, 445)])
 def test_engine_attention_splits_edge(batch, length):
     """Short contexts run a (row, head)'s attention in one block, longer ones in split
-    keys with a merge: steps that cross the line (448 cached keys for one row, 896 for
-    several), for the encoder and NT decoder; the LM module and MB window stay below it."""
+    keys with a merge: steps that cross the line (224 cached float32 keys for one row, 448
+    for several), for the encoder and NT decoder; the LM module and MB window stay below it."""
     raw = synth.make_weights(synth.SMALL_F32, seed=5, gain_jitter=0.2, logit_gain=10.0)
     W = oracle.to_float64(raw)
     dec = new_decoder(synth.SMALL_F32, raw, batch, 1000)
