@@ -105,8 +105,8 @@ hipError_t launch_linear(const Linear& L, int wdt, float* inv_rms_scratch, hipSt
 // group's 32 hi = bf16(x), then its 32 lo = bf16(x - hi) (4 K bytes, as in float32).  x
 // holds M such rows of ldx values; the row scales rs (M floats, or nullptr: 1) multiply
 // the products, so an RMSNorm's rows are split as x * gain: embedding rows and gains of 8
-// significant bits stay exact.  epi as Linear's, except that SWIGLU writes split rows of
-// ldy values to y.
+// significant bits stay exact.  epi as Linear's (no STORE: the unembedding is no faster on
+// split rows), except that SWIGLU writes split rows of ldy values to y.
 struct PlaneLinear {
   // what the kernel needs before its first load comes first (two 64-byte lines)
   const uint16_t* x;
@@ -134,6 +134,10 @@ struct PlaneLinear {
 // Whether a linear of this shape (bfloat16 weights) runs on split rows; n_mat: rows of
 // one matrix of a fused weight (N otherwise).
 bool planes_fit(int M, int N, int K, int n_mat);
+// Whether the linears of a block (or of one MLP head) of M rows are faster on split rows
+// than on launch_linear's tiles.
+bool planes_layer(int M, int d, int d_ff);
+bool planes_head(int M, int d, int d_ff);
 hipError_t launch_planes(const PlaneLinear& P, hipStream_t st, const Ev& ev = Ev());
 // Tile (128 or 256) and K splits launch_planes takes for a shape, and the launch at a
 // given choice.

@@ -334,7 +334,6 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
   } else {
     float* const Y = P.epi.Y;
     const size_t ldy = (size_t)P.epi.ldy;
-    const bool add = kind == EPI_RESID;
     static_for<TI>([&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;
 #pragma unroll
@@ -344,7 +343,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
         if (full || m < M) {
           float old[TJ];
 #pragma unroll
-          for (int j = 0; j < TJ; ++j) old[j] = add ? y[j * 32] : 0.f;
+          for (int j = 0; j < TJ; ++j) old[j] = y[j * 32];
           static_for<TJ>([&](auto jc) __attribute__((always_inline)) {
             constexpr int j = decltype(jc)::value;
             y[j * 32] = old[j] + acc[i][j][r];
@@ -468,7 +467,7 @@ hipError_t planes_launch_t(PTile<WM, WN, TI, TJ>, const PlaneLinear& P, int ks, 
       case EPI_SWIGLU: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_SWIGLU>);
       case EPI_QKV: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_QKV>);
       case EPI_RESID: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_RESID>);
-      default: return go(gemm_planes_kernel<WM, WN, TI, TJ, EPI_STORE>);
+      default: return hipErrorInvalidValue;
     }
   }
 }
@@ -503,6 +502,41 @@ PlanesPlan planes_plan(const PlaneLinear& P) {
   return {128, ks};
 }
 
+namespace {
+// K splits of a residual product (d columns) of M rows over K.
+int resid_ks(int M, int d, int K) {
+  PlaneLinear P{};
+  float part;  // the rule only asks whether there is scratch
+  P.kind = EPI_RESID; P.M = M; P.N = d; P.K = K; P.part = &part;
+  P.mats.rows = d; P.mats.mode = MAT_SINGLE;
+  return planes_plan(P).ks;
+}
+}  // namespace
+
+// Split rows against the tiles of kernels.hip, us per layer of a prompt pass (off -> on):
+// a layer whose residual products split K norms their rows in the kernel that adds the
+// parts, so it takes no launch more, and the line lies where 128-row tiles are filled
+// (d = 1024: M = 65 78.3 -> 80.1, 96 81.9 -> 81.9, 128 91.8 -> 85.4; d = 768: M = 128
+// 76.5 -> 79.5, 192 84.3 -> 83.3; d = 2048: M = 65 139 -> 122).  The others split their
+// rows in two launches of their own and walk K whole, which long passes repay (d = 128:
+// M = 512 65.9 -> 79.9, 8192 128 -> 127, 32768 304 -> 270; d = 256: M = 1024 89 -> 109,
+// 4096 133 -> 128; d = 384: 2048 148 -> 146; d = 576: 512 99 -> 115, 1024 142 -> 138;
+// d = 960: 256 106 -> 131, 512 152 -> 144; d = 1600: 128 128 -> 171, 256 189 -> 175).
+// Both lines follow M d sqrt(d_ff) over these widths.
+bool planes_layer(int M, int d, int d_ff) {
+  if (!planes_fit(M, 3 * d, d, d) || !planes_fit(M, d, d, d) || !planes_fit(M, 2 * d_ff, d, 2 * d_ff) || !planes_fit(M, d, d_ff, d))
+    return false;
+  const double work = (double)M * d * sqrt((double)d_ff);
+  return work >= (resid_ks(M, d, d) > 1 && resid_ks(M, d, d_ff) > 1 ? 6e6 : 3.2e7);
+}
+
+// One MLP head (gate/up and down, no residual rows to norm before them), off -> on: d =
+// 512 M = 128 75 -> 72, 512 140 -> 142; d = 1024: 65 82.5 -> 82.8, 256 114 -> 108; d =
+// 2048: 65 148 -> 138; d = 128 and 256: 65 +3, 512 no difference.
+bool planes_head(int M, int d, int d_ff) {
+  return planes_fit(M, 2 * d_ff, d, 2 * d_ff) && planes_fit(M, d, d_ff, d) && (double)M * d * sqrt((double)d_ff) >= 1.2e7;
+}
+
 static bool fuse_shape(const PlaneLinear& P) { return P.kind == EPI_RESID && P.epi.ldy == P.N; }
 
 bool planes_fuses_norm(const PlaneLinear& P) { return fuse_shape(P) && planes_plan(P).ks > 1; }
@@ -534,3 +568,9 @@ hipError_t launch_split_rows(const float* x, const float* gain, float eps, uint1
 }
 
 }  // namespace mbp
+
+// For the tests: whether the linears of a block (head = 0) or of an MLP head (1) of M rows
+// run on split rows.
+extern "C" int mbp_check_split_layer(int32_t M, int32_t d, int32_t d_ff, int32_t head) {
+  return head ? mbp::planes_head(M, d, d_ff) : mbp::planes_layer(M, d, d_ff);
+}

@@ -567,25 +567,14 @@ int run_planes(mbp_handle* h, const Linear& L, const uint16_t* x, uint16_t* y, c
   return MBP_OK;
 }
 
-// A product of many rows that no epilogue ties to the layers (the unembedding of a long
-// pass, the MLP heads of a large batch) splits its rows first; sc.O is free then.
-constexpr int kSplitFirstRows = 1024;
-
-bool planes_ok(const mbp_handle* h, const Linear& L) {
-  if (!h->wdt || !planes_fit(L.M, L.N, L.K, L.mats.mode == MAT_QKV ? L.mats.rows : L.N)) return false;
-  // the weights go to LDS in 16-byte pieces
-  for (int i = 0; i < (L.mats.mode == MAT_QKV ? 3 : L.mats.mode == MAT_GATEUP ? 2 : 1); ++i)
-    if (reinterpret_cast<uintptr_t>(L.mats.m[i]) % 16 != 0) return false;
+// Whether a linear's weights can go to LDS in 16-byte pieces, as split rows need.
+bool aligned16(const Mats& m) {
+  for (int i = 0; i < (m.mode == MAT_QKV ? 3 : m.mode == MAT_GATEUP ? 2 : 1); ++i)
+    if (reinterpret_cast<uintptr_t>(m.m[i]) % 16 != 0) return false;
   return true;
 }
 
 int run_linear(mbp_handle* h, Linear L, const Scratch& sc, hipStream_t st) {
-  if (L.M >= kSplitFirstRows && L.epi.kind == EPI_STORE && L.xidx == nullptr && L.gain2 == nullptr && L.K == h->sz.d &&
-      L.ldx == L.K && planes_ok(h, L)) {
-    uint16_t* so = reinterpret_cast<uint16_t*>(sc.O);
-    OTHER(h, launch_split_rows, L.X, L.gain, L.eps, so, sc.inv, L.K, L.M, st);
-    return run_planes(h, L, so, nullptr, sc, st);
-  }
   L.part = sc.gpart;
   float* inv = sc.inv;
   const int cls = linear_is_gemv(L, h->wdt) ? MBP_KCLASS_GEMV : MBP_KCLASS_GEMM;
@@ -781,7 +770,8 @@ int run_stack(mbp_handle* h, const std::vector<BlockW>& layers, const KV& kv, fl
     dn.epi.kind = EPI_RESID; dn.epi.Y = X; dn.epi.ldy = s.d;
     // long passes of bfloat16 models run on split rows (PlaneLinear): each linear's input
     // is split once, by the kernel that produces it, in the place of its float32 rows
-    const bool planes = planes_ok(h, qkv) && planes_ok(h, o) && planes_ok(h, gu) && planes_ok(h, dn);
+    const bool planes = h->wdt && planes_layer(M, s.d, s.dff) && aligned16(qkv.mats) && aligned16(o.mats) &&
+                        aligned16(gu.mats) && aligned16(dn.mats);
 
     if (planes) {
       if (!normed) OTHER(h, launch_split_rows, X, w.attn_norm, h->cfg.rms_eps, so, sc.inv, s.d, M, st);
@@ -1331,7 +1321,7 @@ int draft(mbp_handle* h, int n, float tau, bool threshold, uint8_t* d_cand, floa
       dn.X = sc.Hid; dn.ldx = s.dff; dn.M = B; dn.K = s.dff; dn.N = s.d; dn.gain = nullptr;
       dn.mats.m[0] = w.wd; dn.mats.rows = s.d; dn.mats.mode = MAT_SINGLE;
       dn.epi.kind = EPI_RESID; dn.epi.Y = mlp_out + (size_t)m * s.d; dn.epi.ldy = s.nmax * s.d;
-      if (planes_ok(h, gu) && planes_ok(h, dn)) {
+      if (h->wdt && planes_head(B, s.d, s.dff) && aligned16(gu.mats) && aligned16(dn.mats)) {
         uint16_t* so = reinterpret_cast<uint16_t*>(sc.O);
         uint16_t* sh = reinterpret_cast<uint16_t*>(sc.Hid);
         OTHER(h, launch_split_rows, h1, w.norm, c.rms_eps, so, sc.inv, s.d, B, h->st);

@@ -1,27 +1,36 @@
-"""GPU parity of the long-pass path on split rows (bfloat16 models, passes of 65 rows or
-more) at the sizes where its tiles, K splits and row maps can go wrong.  Logits against
-the oracle within 1e-3 at logit gain 1 and |logit| of a few units: keys and values are
-kept in float16 (2^-11 relative), which over the six layers of these models moves a
-logit by a few 1e-4; activations enter the products with 16 significant bits."""
+"""GPU parity of the long-pass path on split rows (bfloat16 models) at the sizes where its
+tiles, K splits and row maps can go wrong.  Logits against the oracle within 1e-3 at logit
+gain 1 and |logit| of a few units: keys and values are kept in float16 (2^-11 relative),
+which over the layers of these models moves a logit by a few 1e-4; activations enter the
+products with 16 significant bits.  Every test asks the library's rule whether its passes
+run on split rows."""
+import numpy as np
 import pytest
+import torch  # noqa: F401  (before the library is loaded: both use torch's HIP runtime)
 
 import oracle
+import paper_2608_15454_amd as mbp
 import synth
-from gpu_harness import forced_run, new_decoder
+from gpu_harness import new_decoder
 from test_gpu_forward import check
 
 pytestmark = pytest.mark.gpu
 
-# d = 256: column tiles of 128 and (gate / up) 256; d = 128 with heads of 32: the prefill
-# attention's general kernel writes the split rows
-D256 = synth.SMALL_F32.replace(dtype="bf16")
-D128 = synth.ModelConfig(d_model=128, n_heads=4, n_enc=1, n_lm=1, n_nb=1, n_mb=1, head="lca", dtype="bf16")
+# heads of 64, and of 32 (the prefill attention's general kernel writes the split rows)
+D64 = synth.ModelConfig(d_model=1024, n_heads=16, n_enc=1, n_lm=1, n_nb=1, n_mb=1, head="lca", dtype="bf16")
+D32 = D64.replace(n_heads=32)
 TOL = 1e-3
 
 
-@pytest.mark.parametrize("model,T", [(D256, 64), (D256, 65), (D256, 127), (D256, 128), (D256, 129), (D256, 257),
-                                     (D256, 700), (D128, 65), (D128, 200)])
+def on_split_rows(model, M, head=0):
+    L = mbp.lib()
+    return bool(L.mbp_check_split_layer(M, model.d_model, model.d_ff or 4 * model.d_model, head))
+
+
+@pytest.mark.parametrize("model,T", [(D64, 65), (D64, 95), (D64, 127), (D64, 128), (D64, 129), (D64, 257), (D64, 700),
+                                     (D32, 100), (D32, 200)])
 def test_forward_row_edges(model, T):
+    assert on_split_rows(model, T) == (T > 90)
     raw = synth.make_weights(model, seed=T, gain_jitter=0.3)
     dec = new_decoder(model, raw, 1, T + 8)
     check(dec, oracle.to_float64(raw), model, synth.make_prompt(T, T), TOL)
@@ -32,19 +41,31 @@ def test_forward_cache_types(kw):
     """Float32 and bfloat16 caches take the general prefill attention; bfloat16 keeps 8
     bits of a key, 8 times the error of float16.  Passes of 100 rows: key blocks that lie
     below, across and above a tile's first query at odd offsets."""
-    raw = synth.make_weights(D256, seed=2, gain_jitter=0.3)
     T = 333 if "max_chunk" in kw else 150
-    dec = new_decoder(D256, raw, 1, T + 50, **kw)
-    check(dec, oracle.to_float64(raw), D256, synth.make_prompt(2, T), TOL * (8 if kw.get("kv_dtype") == 1 else 1))
+    assert on_split_rows(D64, min(T, 100))
+    raw = synth.make_weights(D64, seed=2, gain_jitter=0.3)
+    dec = new_decoder(D64, raw, 1, T + 50, **kw)
+    check(dec, oracle.to_float64(raw), D64, synth.make_prompt(2, T), TOL * (8 if kw.get("kv_dtype") == 1 else 1))
 
 
-@pytest.mark.parametrize("batch,head", [(65, "lca"), (70, "lca"), (66, "mlp")])
+@pytest.mark.parametrize("batch,head", [(97, "lca"), (129, "lca"), (190, "mlp")])
 def test_decode_many_rows(batch, head):
-    """Commits of 65 rows and more: the decode attention (one split, and several merged)
-    writes split rows; the MLP heads of a large batch run on them."""
-    model = D256.replace(head=head, n_mb=2)
+    """Commits of many rows, one byte each: the decode attention (one split, and several
+    merged) writes split rows; the MLP heads of a large batch run on them."""
+    model = D64.replace(head=head)
+    assert on_split_rows(model, batch) and (head == "lca" or on_split_rows(model, batch, 1))
     raw = synth.make_weights(model, seed=batch, gain_jitter=0.3)
     W = oracle.to_float64(raw)
     dec = new_decoder(model, raw, batch, 330)
-    prompts = [synth.make_prompt(b, 300 if b == 3 else 6 + b % 9) for b in range(batch)]
-    forced_run(dec, W, model, prompts, 2, 3, 0.75, tol=TOL, label=f"{head} {batch}")
+    xs = [[int(v) for v in synth.make_prompt(b, 300 if b == 3 else 6 + b % 9)] for b in range(batch)]
+    dec.prefill(xs)
+    for step in range(2):
+        dec.decode_step(2, 0.75)
+        logits = dec.logits().double().cpu().numpy()
+        for b in (0, 3, 63, 64, 95, batch - 1):
+            err = np.max(np.abs(logits[b] - oracle.step_logits(W, model, xs[b], 2)))
+            assert err <= TOL, f"step {step} row {b}: {err:.3g}"
+        acc = [[(7 * b + 32 * (b % 3)) % 256] for b in range(batch)]
+        dec.accept(acc)
+        for x, a in zip(xs, acc):
+            x += a
