@@ -160,8 +160,9 @@ bool linear_is_gemv(const Linear& L, int wdt);
 hipError_t launch_attn_decode(const Attn& a, int kvt, int max_kv, float* part, int64_t part_floats, hipStream_t st,
                               const Ev& ev = Ev());
 // Tiled causal attention for long runs of consecutive slots of one batch row.
-// tiles: device int32 [ntiles*2] = (first token, count <= 64) with consecutive slots.
-hipError_t launch_attn_prefill(const Attn& a, int kvt, const int32_t* tiles, int ntiles, hipStream_t st,
+// tiles: device int32 [ntiles*2] = (first token, count <= 64) with consecutive slots;
+// max_kv: the pass's largest kvlen.
+hipError_t launch_attn_prefill(const Attn& a, int kvt, const int32_t* tiles, int ntiles, int max_kv, hipStream_t st,
                                const Ev& ev = Ev());
 
 hipError_t launch_embed(const void* emb, int wdt, const int32_t* bytes, float* X, int d, int M, hipStream_t st,

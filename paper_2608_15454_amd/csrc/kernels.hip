@@ -928,7 +928,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // 8 (l / 32) .. +7 of each 16-wide k step.  K tiles are loaded straight to LDS one block
 // ahead (no registers hold them).  Three waves per SIMD: 168 VGPRs and 8 bytes of scratch
 // (two waves per SIMD need no scratch and measure slower).
-constexpr int kPrefillSplitBelow = 3072, kPrefillFourUpTo = 256;  // blocks of the one-group grid
 
 template <int KG, bool SPLIT>
 __global__ __launch_bounds__(128 * KG, KG == 4 ? 2 : 3) void attn_prefill_mfma_kernel(Attn a, const int32_t* tiles) {
@@ -2121,17 +2120,25 @@ hipError_t attn_decode_t(const Attn& a, int max_kv, float* part, int64_t part_fl
   return attn_decode_dh<KV, 32>(a, max_kv, part, part_floats, st, ev);
 }
 
+// Key groups of the MFMA prefill attention for `blocks` blocks (tiles x heads).  A grid
+// that fills the compute units a few times over runs each tile's keys in one group; a
+// smaller one (one long sequence) splits them over two, since its last tiles' key chains
+// would otherwise set the kernel's time; one of at most a block per compute unit over four,
+// once a chain has more than eight key blocks (us in two groups -> four, d = 1024: 100 keys
+// 9.2 -> 11.1, 250 12.2 -> 12.5, 400 14.8 -> 15.2, 600 18.7 -> 18.6, 1000 23.7 -> 21.0;
+// d = 256: 300 12.4 -> 13.1, 500 15.2 -> 14.6, 4000 72 -> 58).  Under a group mask a tile
+// walks its own and the previous group's keys only.
+static int prefill_groups(int64_t blocks, int max_kv, bool group_mask) {
+  if (blocks >= 3072) return 1;
+  return blocks <= 256 && max_kv > 512 && !group_mask ? 4 : 2;
+}
+
 template <typename KV>
-hipError_t attn_prefill_t(const Attn& a, const int32_t* tiles, int ntiles, hipStream_t st, const Ev& ev) {
+hipError_t attn_prefill_t(const Attn& a, const int32_t* tiles, int ntiles, int max_kv, hipStream_t st, const Ev& ev) {
   const dim3 grid(ntiles, a.H);
   if constexpr (std::is_same<KV, _Float16>::value)
     if (a.dh == 64) {
-      // a grid that fills the compute units a few times over runs each tile's keys in one
-      // group; a smaller one (one long sequence) splits them over two groups, since its
-      // last tiles' key chains would otherwise set the kernel's time
-      // and one of at most a block per compute unit over four
-      const int64_t blocks = (int64_t)ntiles * a.H;
-      const int kg = blocks <= kPrefillFourUpTo ? 4 : blocks < kPrefillSplitBelow ? 2 : 1;
+      const int kg = prefill_groups((int64_t)ntiles * a.H, max_kv, a.grp_tab != nullptr);
       auto kern = a.split ? (kg == 4 ? attn_prefill_mfma_kernel<4, true> : kg == 2 ? attn_prefill_mfma_kernel<2, true> : attn_prefill_mfma_kernel<1, true>)
                           : (kg == 4 ? attn_prefill_mfma_kernel<4, false> : kg == 2 ? attn_prefill_mfma_kernel<2, false> : attn_prefill_mfma_kernel<1, false>);
       return klaunch(kern, grid, dim3(128 * kg), 0, st, ev.start, ev.stop, a, tiles);
@@ -2163,12 +2170,12 @@ hipError_t launch_attn_decode(const Attn& a, int kvt, int max_kv, float* part, i
   return attn_decode_t<float>(a, max_kv, part, part_floats, st, ev);
 }
 
-hipError_t launch_attn_prefill(const Attn& a, int kvt, const int32_t* tiles, int ntiles, hipStream_t st,
+hipError_t launch_attn_prefill(const Attn& a, int kvt, const int32_t* tiles, int ntiles, int max_kv, hipStream_t st,
                                const Ev& ev) {
   if (ntiles <= 0) return hipSuccess;
-  if (kvt == 2) return attn_prefill_t<_Float16>(a, tiles, ntiles, st, ev);
-  if (kvt == 1) return attn_prefill_t<uint16_t>(a, tiles, ntiles, st, ev);
-  return attn_prefill_t<float>(a, tiles, ntiles, st, ev);
+  if (kvt == 2) return attn_prefill_t<_Float16>(a, tiles, ntiles, max_kv, st, ev);
+  if (kvt == 1) return attn_prefill_t<uint16_t>(a, tiles, ntiles, max_kv, st, ev);
+  return attn_prefill_t<float>(a, tiles, ntiles, max_kv, st, ev);
 }
 
 hipError_t launch_embed(const void* emb, int wdt, const int32_t* bytes, float* X, int d, int M, hipStream_t st,
@@ -2288,3 +2295,8 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
 }
 
 }  // namespace mbp
+
+// For the tests: the key groups of a prefill attention grid.
+extern "C" int mbp_check_prefill_groups(int32_t blocks, int32_t max_kv, int32_t group_mask) {
+  return mbp::prefill_groups(blocks, max_kv, group_mask != 0);
+}
