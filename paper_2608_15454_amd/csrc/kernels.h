@@ -113,10 +113,10 @@ struct PlaneLinear {
   const float* rs;
   int32_t ldx, M, K, N;
   int32_t kind;
-  // set by launch_planes_at: K splits, whether rs is set, the grid's column blocks, and its
-  // order (log2 of the L2 group's row blocks and the reciprocal of a group's blocks; 0:
-  // plain order)
-  int32_t ksplit, scaled, cb, grl;
+  // set by launch_planes_at: K splits, whether rs is set, the column blocks of the grid and
+  // of one matrix (cm), and the grid's order (log2 of the L2 group's row blocks and the
+  // reciprocal of a group's blocks; 0: plain order)
+  int32_t ksplit, scaled, cb, cm, grl;
   uint32_t ginv;
   Mats mats;
   uint16_t* y;

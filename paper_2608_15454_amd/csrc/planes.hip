@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
     bx = rem >> P.grl;
     by = xcd + 8 * ((g << P.grl) + (rem & ((1 << P.grl) - 1)));
   }
-  const int m0 = by * BM, n0 = bx * BN;
+  const int m0 = by * BM;
   const int K = P.K, M = P.M;
   // this block's steps: K / ksplit columns from z K / ksplit on; nk is even and >= 4
   const int nk = EK == kEpiPart ? K / kBK / P.ksplit : K / kBK;
@@ -109,15 +109,20 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
   // lane holds both values of its pairs.  wbase: the matrix (of the tile, or of the half)
   // and its first row; step: rows between columns.
   const bool gu = kind == EPI_SWIGLU;
-  const int which = kind == EPI_QKV || (kind == kEpiPart && P.mats.mode == MAT_QKV) ? (n0 >= P.mats.rows) + (n0 >= 2 * P.mats.rows) : 0;  // a tile lies in one of q, k, v
+  const int which = kind == EPI_QKV || (kind == kEpiPart && P.mats.mode == MAT_QKV) ? (bx >= P.cm) + (bx >= 2 * P.cm) : 0;  // a tile lies in one of q, k, v
   const char* const wm0 = reinterpret_cast<const char*>(which == 0 ? P.mats.m[0] : which == 1 ? P.mats.m[1] : P.mats.m[2]);
   const char* const wm1 = reinterpret_cast<const char*>(gu ? P.mats.m[1] : wm0);
-  const int nrow = gu ? n0 >> 1 : n0 - which * P.mats.rows;
+  // the tile's first column in its matrix, and in the fused order.  A matrix of an odd
+  // multiple of 64 rows ends inside its last 128 tile, on a wave boundary: that tile's
+  // second wave column repeats the first one's weights and stores nothing (a forward of
+  // 2048 rows, on 64 x 64 tiles without this: d = 960 2.36 -> 1.74 ms, d = 1600 5.48 -> 3.24).
+  const int ncol = (bx - which * P.cm) * BN, n0 = ncol + which * P.mats.rows, nrow = gu ? ncol >> 1 : ncol;
+  const int wcols = WN == 2 && WM == 2 && !gu && ncol + 32 * TJ >= P.mats.rows ? 1 : WN;  // wave columns inside the matrix
   const uint32_t vrow = (uint32_t)(lane >> 3) * (uint32_t)(pair && !gu ? 2 : 1) * (uint32_t)K * 2;
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
-    const int c = (wave * GB + g) * 8, cc = c % (32 * TJ), odd = cc / (16 * TJ), in = cc % (16 * TJ), wc = c / (32 * TJ);
-    const int r = !pair ? nrow + c : gu ? nrow + wc * 16 * TJ + in : nrow + wc * 32 * TJ + 2 * in + odd;
+    const int c = (wave * GB + g) * 8, cc = c % (32 * TJ), odd = cc / (16 * TJ), in = cc % (16 * TJ), wc = min(c / (32 * TJ), wcols - 1);
+    const int r = gu ? nrow + wc * 16 * TJ + in : nrow + wc * 32 * TJ + (pair ? 2 * in + odd : cc);
     sb[g] = (pair && odd ? wm1 : wm0) + ((size_t)r * K + kz * 32) * 2;
     vb[g] = vrow + (((lane & 7) ^ (((c + (lane >> 3)) >> 1) & 7)) * 16);
   }
@@ -220,6 +225,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_planes_kernel(PlaneLinea
     w = T::kW - w;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land after the block has ended
+  if (wn >= wcols) return;
   // The epilogue's row and column numbers start here: computed from the same values as the
   // loop's, the compiler would move them above the loop and spill.
   int em = m0 + wm * 32 * TI, en = n0, el = lane, ew = wn, ec = nrow;
@@ -437,6 +443,11 @@ __global__ __launch_bounds__(256) void finish_split_kernel(const float* part, in
   if (tid == 0) rs[row] = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
 }
 
+// Column blocks of BN: a tile lies in one matrix of a fused QKV weight.
+int column_blocks(const PlaneLinear& P, int BN) {
+  return P.mats.mode == MAT_QKV ? 3 * ((P.mats.rows + BN - 1) / BN) : (P.N + BN - 1) / BN;
+}
+
 template <int WM, int WN, int TI, int TJ>
 hipError_t planes_launch_t(PTile<WM, WN, TI, TJ>, const PlaneLinear& P, int ks, hipStream_t st, const Ev& ev) {
   using T = PTile<WM, WN, TI, TJ>;
@@ -444,7 +455,8 @@ hipError_t planes_launch_t(PTile<WM, WN, TI, TJ>, const PlaneLinear& P, int ks, 
   Q.ksplit = ks;
   Q.scaled = P.rs != nullptr;
   if (!Q.scaled) Q.rs = reinterpret_cast<const float*>(P.x);  // M readable floats
-  Q.cb = P.N / T::BN;
+  Q.cm = (P.mats.rows + T::BN - 1) / T::BN;
+  Q.cb = column_blocks(P, T::BN);
   const int rb = (P.M + T::BM - 1) / T::BM;
   // row blocks per L2 group: about 2 MiB of activation rows, a power of two; the kernel
   // divides block numbers below 2^16 by the group's blocks with a rounded-up reciprocal
@@ -475,7 +487,7 @@ hipError_t planes_launch_t(PTile<WM, WN, TI, TJ>, const PlaneLinear& P, int ks, 
 }  // namespace
 
 bool planes_fit(int M, int N, int K, int n_mat) {
-  return M >= kPlanesMinRows && N % 128 == 0 && n_mat % 128 == 0 && K % 64 == 0 && K >= 128;
+  return M >= kPlanesMinRows && N % 64 == 0 && n_mat % 64 == 0 && K % 64 == 0 && K >= 128;
 }
 
 // The 256 tile fills the chip with one block per compute unit, the 128 tile with two; a
@@ -487,7 +499,7 @@ bool planes_fit(int M, int N, int K, int n_mat) {
 // the blocks stay below 200 (M = 740, N = 1024, K = 4096: 48 us whole, 30 / 27 / 29 us
 // in 2 / 4 / 8 parts; M = 512: 48, 28 / 21 / 24 us), a part keeping 256 columns.
 PlanesPlan planes_plan(const PlaneLinear& P) {
-  const int64_t t128 = (int64_t)(P.N / 128) * ((P.M + 127) / 128);
+  const int64_t t128 = (int64_t)column_blocks(P, 128) * ((P.M + 127) / 128);
   const int nmat = P.mats.mode == MAT_QKV ? P.mats.rows : P.N;
   if (P.N % 256 == 0 && nmat % 256 == 0) {
     const int64_t t256 = (int64_t)(P.N / 256) * ((P.M + 255) / 256);

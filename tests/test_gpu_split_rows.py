@@ -36,6 +36,17 @@ def test_forward_row_edges(model, T):
     check(dec, oracle.to_float64(raw), model, synth.make_prompt(T, T), TOL)
 
 
+@pytest.mark.parametrize("d,heads,T", [(576, 9, 1250), (960, 30, 600), (960, 15, 641)])
+def test_forward_odd_widths(d, heads, T):
+    """d an odd multiple of 64: the last tile of q, k, v, of the output and of the down
+    product holds 64 columns."""
+    model = D64.replace(d_model=d, n_heads=heads, d_ff=0).replace(d_ff=4 * d)
+    assert on_split_rows(model, T)
+    raw = synth.make_weights(model, seed=T, gain_jitter=0.3)
+    dec = new_decoder(model, raw, 1, T + 8)
+    check(dec, oracle.to_float64(raw), model, synth.make_prompt(T, T), TOL)
+
+
 @pytest.mark.parametrize("kw", [dict(engine=False), dict(kv_dtype=0), dict(kv_dtype=1), dict(max_chunk=100)])
 def test_forward_cache_types(kw):
     """Float32 and bfloat16 caches take the general prefill attention; bfloat16 keeps 8

@@ -15,7 +15,9 @@ def layer(M, d, d_ff=None, head=0):
 @pytest.mark.parametrize("d,M,on", [
     (128, 128, False), (128, 1024, False), (128, 32768, True), (256, 65, False), (256, 1024, False), (256, 8192, True),
     (384, 512, False), (384, 4096, True), (512, 65, False), (512, 512, True), (768, 96, False), (768, 256, True),
-    (1024, 64, False), (1024, 112, True), (1024, 531, True), (2048, 65, True)])
+    (1024, 64, False), (1024, 112, True), (1024, 531, True), (2048, 65, True),
+    # widths of an odd multiple of 64, whose matrices end inside a tile
+    (576, 512, False), (576, 2048, True), (960, 256, False), (960, 1024, True), (1088, 1024, True), (1600, 512, True)])
 def test_layers_take_the_faster_path(d, M, on):
     assert layer(M, d) == on
 
