@@ -1939,7 +1939,13 @@ constexpr int gemv_r(int kc) { return kc <= 4 ? 4 : (kc == 8 ? 2 : 1); }
 constexpr int gemv_mr(int kc) { return kc <= 2 ? 4 : (kc <= 8 ? 2 : 1); }
 
 // Columns per lane for K below one chunk of 16-byte lanes: K = 128, and K = 256 of
-// bfloat16 weights (0: K is not that narrow).
+// bfloat16 weights (0: K is not that narrow).  Up to 32 rows: every wave reads all of
+// them for its four weight rows, 64 x 64 tiles once (float32, K = 128, N = 128 to 1024,
+// us a product, tiles -> GEMV: 4 rows 17 -> 5, 16 rows 16.5 -> 7.5, 32 rows 17 -> 11.5;
+// a forward of 48 rows 456 -> 486, of 64 rows 473 -> 564).  Bfloat16 products of more
+// than 16 rows are on the matrix cores anyway.
+constexpr int kGemvNarrowMaxRows = 32;
+
 template <typename W>
 constexpr int gemv_narrow_vec(int K) {
   return K == 128 || (K == 256 && sizeof(W) == 2) ? K / 64 : 0;
@@ -1949,7 +1955,7 @@ template <typename W>
 bool gemv_fits(const Linear& L) {
   constexpr int VEC = WT<W>::VEC;
   if (L.M > kGemvMaxRows) return false;
-  if (gemv_narrow_vec<W>(L.K) != 0) return L.N % 4 == 0;
+  if (gemv_narrow_vec<W>(L.K) != 0) return L.N % 4 == 0 && L.M <= kGemvNarrowMaxRows;
   if (L.K % (64 * VEC) != 0) return false;
   const int kc = L.K / (64 * VEC);
   if (kc != 1 && kc != 2 && kc != 4 && kc != 8 && kc != 16) return false;
@@ -2040,8 +2046,6 @@ hipError_t linear_t(const Linear& L, float* inv_rms, hipStream_t st, const Ev& e
     return launch_gemm_finish(L, ks, st, ev);
   }
   if (gemv_fits<W>(L)) {
-    // narrow K: these products (models of d = 128, bfloat16 ones of d = 256) used to take
-    // the 64 x 64 tile, whose few blocks walk K alone (N = 384..1024, K = 128: 12.7 us)
     const int nv = gemv_narrow_vec<W>(L.K);
     if (nv == 2) return gemv_launch_r<W, 1, 4, 2>(L, st, ev);
     if constexpr (sizeof(W) == 2)
@@ -2295,6 +2299,13 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
 }
 
 }  // namespace mbp
+
+// For the tests: whether a plain product of M rows takes the GEMV.
+extern "C" int mbp_check_gemv(int32_t wdt, int32_t M, int32_t N, int32_t K) {
+  mbp::Linear L{};
+  L.M = M; L.N = N; L.K = K; L.epi.kind = mbp::EPI_STORE;
+  return mbp::linear_is_gemv(L, wdt);
+}
 
 // For the tests: the key groups of a prefill attention grid.
 extern "C" int mbp_check_prefill_groups(int32_t blocks, int32_t max_kv, int32_t group_mask) {

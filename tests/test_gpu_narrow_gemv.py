@@ -3,8 +3,10 @@ models' decode passes: 1 row, 2, and more than one group of 4, with the fused ep
 Float32 within 1e-5 as everywhere; bfloat16 models keep float16 keys and values (2^-11
 relative, a few 1e-4 of a logit over their layers): 1e-3."""
 import pytest
+import torch  # noqa: F401  (before the library is loaded: both use torch's HIP runtime)
 
 import oracle
+import paper_2608_15454_amd as mbp
 import synth
 from gpu_harness import forced_run, new_decoder
 
@@ -18,6 +20,7 @@ D256 = synth.SMALL_F32.replace(dtype="bf16", n_lm=1)
 @pytest.mark.parametrize("model,tol", [(F32, 1e-5), (D128, 1e-3), (D256, 1e-3), (D256.replace(head="mlp"), 1e-3)])
 @pytest.mark.parametrize("batch", [1, 2, 7])
 def test_narrow_products(model, tol, batch):
+    assert mbp.lib().mbp_check_gemv(model.dtype == "bf16", batch, 3 * model.d_model, model.d_model)
     raw = synth.make_weights(model, seed=batch, gain_jitter=0.3)
     dec = new_decoder(model, raw, batch, 80)
     prompts = [synth.make_prompt(b, 24 + 5 * b) for b in range(batch)]

@@ -1,5 +1,5 @@
-"""Which passes run on split rows, and how the prefill attention splits its keys: the
-library's rules alone, no GPU."""
+"""Which passes run on split rows, which narrow products on the GEMV, and how the prefill
+attention splits its keys: the library's rules alone, no GPU."""
 import pytest
 import torch  # noqa: F401  (before the library is loaded: both use torch's HIP runtime)
 
@@ -34,3 +34,11 @@ def test_mlp_heads_take_the_faster_path(d, M, on):
     (3071, 4096, 0, 2), (3072, 64, 0, 1)])
 def test_prefill_attention_key_groups(blocks, max_kv, mask, groups):
     assert mbp.lib().mbp_check_prefill_groups(blocks, max_kv, mask) == groups
+
+
+# (weights, K, rows): float32 products of K = 128 measured slower on the GEMV from 48 rows on
+@pytest.mark.parametrize("wdt,K,M,on", [
+    (0, 128, 1, True), (0, 128, 32, True), (0, 128, 33, False), (0, 128, 64, False), (0, 256, 64, True),
+    (1, 128, 16, True), (1, 128, 17, False), (1, 256, 16, True), (1, 256, 17, False)])
+def test_narrow_products(wdt, K, M, on):
+    assert bool(mbp.lib().mbp_check_gemv(wdt, M, 1024, K)) == on
