@@ -662,25 +662,32 @@ double stack_bytes(const mbp_handle* h, int nlayers, int M, double kv_rows) {
   return per_layer * nlayers;
 }
 
-// The engine call of a pass over `grid` blocks: the cached keys per attention split
-// are as few as keep the (row, head, split) items within one per block, so the cache
-// reads are spread over every block.  False when the pass does not fit the engine.
+// Attention splits of an engine pass of M rows over `grid` blocks, and the cached keys of
+// one (chunk): as few as keep the (row, head, split) items within one per block, so the
+// cache reads are spread over every block.  Short contexts: one block per (row, head)
+// takes all keys (one split), which saves the merge step, up to one load round of the
+// block's waves (448 keys, 224 in float32), two from four rows on, whose merges do more and
+// whose items fill the blocks (engine us a step, split -> one block, eight d = 1024 layers
+// of float16 keys: 1 row, 430 keys 222 -> 220, 460 222 -> 226, 850 230 -> 235; 2 rows, 430
+// 270 -> 259, 460 267 -> 267, 850 272 -> 279; 3 rows, 850 305 -> 310; 4 rows, 850 313 ->
+// 311; 8 rows, 850 414 -> 386; 16 rows, 850 683 -> 632; float32 keys, d = 256: 1 row, 210
+// 127 -> 123, 300 129 -> 131; 4 rows, 420 165 -> 167; 16 rows, 420 258 -> 251).
+int engine_splits(int M, int H, int max_ns, int grid, bool f32_keys, int* chunk) {
+  const int cached_splits = std::max(1, grid / (M * H) - 1);
+  *chunk = std::max(64, (max_ns + cached_splits - 1) / cached_splits + 63) / 64 * 64;
+  const int round = f32_keys ? 224 : 448;
+  return max_ns <= (M < 4 ? round : 2 * round) ? 1 : (max_ns + *chunk - 1) / *chunk + 1;
+}
+
+// The engine call of a pass over `grid` blocks.  False when the pass does not fit the
+// engine.
 bool engine_call(const mbp_handle* h, const EngStack* es, const EIo& io, const Tok& tok, const int32_t* first,
                  const int32_t* first_slot, int32_t max_ns, const int32_t* grp_tab, int grid, ECall* c) {
   const Sizes& s = h->sz;
   if (!h->engine || es == nullptr || es->nops == 0 || tok.M > kEngineMaxRows || grid <= 0) return false;
   if (tok.M > 1 && !engine_multi_row(h->eng_shape)) return false;
-  // Short contexts: one block per (row, head) takes all keys (S = 1), which saves the
-  // merge step.  Up to one load round of the block's waves (448 keys, 224 in float32) for a single row,
-  // two for several, whose merge does more (generation of 2 bytes a step on ~200 latents,
-  // batch 1: 10.77 -> 10.61 ms; batch 8 on 130: 24.85 -> 24.10 at 448, 23.65 at 896 with
-  // contexts of 900 bytes; batch 1 on ~790 latents: 24.13 ms split, 24.39 in one block,
-  // whose 100 KB of keys and values hold its query poll back).
-  const int items_per_split = tok.M * s.H;
-  const int cached_splits = std::max(1, grid / items_per_split - 1);
-  const int chunk = std::max(64, (max_ns + cached_splits - 1) / cached_splits + 63) / 64 * 64;
-  const int round = h->cfg.kv_dtype == MBP_F32 ? 224 : 448;
-  const int S = max_ns <= (tok.M == 1 ? round : 2 * round) ? 1 : (max_ns + chunk - 1) / chunk + 1;
+  int chunk;
+  const int S = engine_splits(tok.M, s.H, max_ns, grid, h->cfg.kv_dtype == MBP_F32, &chunk);
   if (S > s.Esplit) return false;
   *c = ECall{};
   c->io = io;
@@ -2239,3 +2246,9 @@ extern "C" void mbp_destroy(mbp_handle* h) {
 }
 
 extern "C" const char* mbp_last_error(const mbp_handle* h) { return h ? h->err.c_str() : "null handle"; }
+
+// For the tests: the attention splits of an engine pass.
+extern "C" int mbp_check_engine_splits(int32_t M, int32_t H, int32_t max_ns, int32_t grid, int32_t f32_keys) {
+  int chunk;
+  return engine_splits(M, H, max_ns, grid, f32_keys != 0, &chunk);
+}

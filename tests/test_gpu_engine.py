@@ -9,8 +9,10 @@ for passes of at most 16 token rows).
 Every test also checks that engine launches ran (timing class "engine")."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (before the library is loaded: both use torch's HIP runtime)
 
 import oracle
+import paper_2608_15454_amd as mbp
 import synth
 from gpu_harness import (SELF_VERIFY, THRESHOLD, base_tol, forced_run, free_run, new_decoder)
 
@@ -122,14 +124,21 @@ def test_engine_matches_per_kernel_path_d1024():
     assert np.array_equal(outs[0], outs[1])
 
 
-@pytest.mark.parametrize("batch,length", [(1, 222), (2, 445)])
-def test_engine_attention_splits_edge(batch, length):
-    """Short contexts run a (row, head)'s attention in one block, longer ones in split
-    keys with a merge: steps that cross the line (224 cached float32 keys for one row, 448
-    for several), for the encoder and NT decoder; the LM module and MB window stay below it."""
-    raw = synth.make_weights(synth.SMALL_F32, seed=5, gain_jitter=0.2, logit_gain=10.0)
+# the last encoder pass below the line between one block per (row, head) and split keys,
+# for float32 keys (224, and 448 from four rows on) and float16 ones (448 and 896)
+@pytest.mark.parametrize("model,batch,length", [(SMALL, 1, 222), (SMALL, 2, 221), (SMALL, 4, 445), (D1024, 1, 446),
+                                                (D1024, 3, 445), (D1024, 4, 893)])
+def test_engine_attention_splits_edge(model, batch, length):
+    """Steps that cross the line at which a (row, head)'s attention goes from one block to
+    split keys with a merge, for the encoder and NT decoder; the LM module and MB window
+    stay below it."""
+    f32 = model is SMALL
+    model = model if f32 else model.replace(n_lm=1)
+    splits = [mbp.lib().mbp_check_engine_splits(batch, model.n_heads, ns, 256, int(f32)) for ns in (length, length + 5)]
+    assert splits[0] == 1 and splits[1] > 1
+    raw = synth.make_weights(model, seed=5, gain_jitter=0.2, logit_gain=10.0 if f32 else 1.0)
     W = oracle.to_float64(raw)
-    dec = new_decoder(synth.SMALL_F32, raw, batch, 1000)
+    dec = new_decoder(model, raw, batch, 1000)
     prompts = [synth.make_prompt(20 + b, length - 3 * b) for b in range(batch)]
-    st = forced_run(dec, W, synth.SMALL_F32, prompts, 5, 3, 0.75, tol=base_tol(synth.SMALL_F32) * 10, timing=True)
+    st = forced_run(dec, W, model, prompts, 5, 3, 0.75, tol=base_tol(model) * (10 if f32 else 1), timing=True)
     assert st.timing["engine"][0] > 0

@@ -1,5 +1,5 @@
-"""Which passes run on split rows, which narrow products on the GEMV, and how the prefill
-attention splits its keys: the library's rules alone, no GPU."""
+"""Which passes run on split rows, which narrow products on the GEMV, and how the prefill and
+engine attention split their keys: the library's rules alone, no GPU."""
 import pytest
 import torch  # noqa: F401  (before the library is loaded: both use torch's HIP runtime)
 
@@ -42,3 +42,13 @@ def test_prefill_attention_key_groups(blocks, max_kv, mask, groups):
     (1, 128, 16, True), (1, 128, 17, False), (1, 256, 16, True), (1, 256, 17, False)])
 def test_narrow_products(wdt, K, M, on):
     assert bool(mbp.lib().mbp_check_gemv(wdt, M, 1024, K)) == on
+
+
+# rows, cached keys, float32 keys: at two and three rows one block per (row, head) measured
+# slower than split keys from two load rounds of keys on (850 keys: 272 -> 279 us a step)
+@pytest.mark.parametrize("M,max_ns,f32,one", [
+    (1, 448, 0, True), (1, 449, 0, False), (2, 448, 0, True), (2, 850, 0, False), (3, 449, 0, False), (4, 896, 0, True),
+    (4, 897, 0, False), (16, 896, 0, True), (1, 224, 1, True), (2, 225, 1, False), (8, 448, 1, True), (8, 449, 1, False)])
+def test_engine_attention_splits(M, max_ns, f32, one):
+    n = mbp.lib().mbp_check_engine_splits(M, 16, max_ns, 256, f32)
+    assert (n == 1) == one
