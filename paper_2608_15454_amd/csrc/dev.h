@@ -280,7 +280,7 @@ __device__ __forceinline__ float multi_sum(float (&v)[V]) {
 // any LDS read).
 __device__ __forceinline__ void dma16(uint32_t m0, uint32_t voff, const char* sbase) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff), "s"(sbase)
-               : "memory");
+               : "m0", "memory");
 }
 
 // LDS byte address of p, for dma16.

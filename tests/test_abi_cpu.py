@@ -189,3 +189,18 @@ def test_counter_records_follow_code_not_comments(tmp_path):
     for rec in os.listdir(os.path.join(ROOT, "profiles")):
         if rec.endswith("_hbm_counters.md"):
             assert "code sha256: `" in open(os.path.join(ROOT, "profiles", rec)).read(), rec
+
+
+def test_inline_asm_declares_m0():
+    """An asm statement that writes m0 lists it as clobbered: the compiler keeps lane and
+    LDS indices there and would read the asm's value."""
+    import re
+
+    seen = 0
+    for f in sorted(os.listdir(os.path.join(ROOT, "paper_2608_15454_amd", "csrc"))):
+        src = open(os.path.join(ROOT, "paper_2608_15454_amd", "csrc", f)).read()
+        for stmt in re.findall(r"\basm\s+volatile\s*\((.*?)\);", src, flags=re.S):
+            if "m0," in stmt.split("::")[0]:
+                seen += 1
+                assert '"m0"' in stmt.rsplit(":", 1)[1], (f, stmt)
+    assert seen
