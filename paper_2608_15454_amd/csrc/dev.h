@@ -222,9 +222,27 @@ __device__ __forceinline__ float wave_max(float v) { return group_max<64>(v); }
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
 // The same with the hardware exp2 and reciprocal (v_exp_f32 on -x log2 e, v_rcp_f32,
 // each within about 1 ulp): a few ulp from the division form for |x| up to about 20, the
-// exp2 argument's own rounding growing with |x|.  Used where silu is a measurable part
-// of a kernel's time (the SwiGLU epilogue of the large-tile GEMM).
+// exp2 argument's own rounding growing with |x|.  Used in the SwiGLU epilogue of the 256 x
+// 256 tile.
 __device__ __forceinline__ float silu_fast(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+
+// The same with the rounding of the exp2 argument put back into its result and one Newton
+// step on the reciprocal: as near as the division form (maximum relative error over |x| <=
+// 20: 2.4e-7 as that one's, 3.4e-7 with v_exp_f32 a whole ulp off; silu_fast 1.0e-6) at
+// half its instructions.
+// Beyond |x| = 88 the sigmoid is that of 88 (1, or below 1e-38).  Used in the epilogue of
+// the 128 x 128 tile.
+__device__ __forceinline__ float silu_near(float x) {
+  const float c = __builtin_amdgcn_fmed3f(x, -88.f, 88.f);
+  const float t = c * -1.44269504f;
+  const float r = fmaf(c, -1.92596299e-8f, fmaf(c, -1.44269504f, -t));  // -c log2 e - t
+  float e = __builtin_amdgcn_exp2f(t);
+  e = fmaf(e, r * 0.693147181f, e);
+  const float d = 1.0f + e;
+  float y = __builtin_amdgcn_rcpf(d);
+  y = fmaf(fmaf(-d, y, 1.0f), y, y);
+  return x * y;
+}
 
 template <typename W>
 __device__ __forceinline__ const W* mat_row(const Mats& mt, int n, int K) {
