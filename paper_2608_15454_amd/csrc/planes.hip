@@ -629,9 +629,8 @@ extern "C" int mbp_check_product(const MbpCheckProduct* c) {
   if (c->M < 1 || !whole || c->N % 64 || c->rows % 64 || c->K % 64 || c->K < 128) return 1;
   const PlanesPlan plan = c->tile == 0 ? planes_plan(P) : PlanesPlan{c->tile, c->ks};
   if (plan.tile != 128 && (plan.tile != 256 || plan.ks != 1 || c->N % 256 || (c->kind == EPI_QKV ? c->rows : c->N) % 256)) return 1;
-  if (plan.ks < 1 || c->K % (64 * plan.ks) || c->K / plan.ks < 128 || (plan.ks > 1 && c->kind == EPI_SWIGLU) ||
-      (int64_t)plan.ks * c->M * c->N > kGemmPartFloats)
-    return 1;
+  if (plan.ks < 1 || c->K % (64 * plan.ks) || c->K / plan.ks < 128) return 1;
+  if (plan.ks > 1 && (c->kind == EPI_SWIGLU || c->part == nullptr || (int64_t)plan.ks * c->M * c->N > kGemmPartFloats)) return 1;
   hipError_t e = launch_split_rows(c->x, c->gain, c->eps, c->xs, c->rs, c->K, c->M, nullptr);
   if (e == hipSuccess) e = launch_planes_at(P, plan, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);

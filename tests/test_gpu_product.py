@@ -68,3 +68,114 @@ def test_silu_as_near_as_the_division_form():
     assert ((got_hi + got_lo - ref).abs() <= 2.0 ** -16 * ref.abs()).all()
     share = ((got_hi != hi) | (got_lo != lo)).double().mean().item()
     assert share < 0.02, share
+
+
+def rel(K):
+    return 2.0 ** -16 + K * 2.0 ** -23
+
+
+def inputs(M, K, rows, n, gain, seed):
+    """Rows, gain or None, n weight matrices, and float64 products with the sums of their
+    terms' magnitudes."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn(M, K, generator=gen, device="cuda")
+    g = 1 + 0.3 * torch.randn(K, generator=gen, device="cuda") if gain else None
+    w = [(torch.randn(rows, K, generator=gen, device="cuda") * K ** -0.5).bfloat16() for _ in range(n)]
+    x64 = x.double()
+    if gain:
+        x64 = x64 * g.double() / (x64.pow(2).mean(1, keepdim=True) + 1e-6).sqrt()
+    prods = [x64 @ m.double().t() for m in w]
+    mags = [x64.abs() @ m.double().abs().t() for m in w]
+    return x, {"gain": g} if gain else {}, w, prods, mags
+
+
+def close(got, ref, bound):
+    bad = (got.double() - ref).abs() > bound
+    assert not bad.any(), (bad.nonzero()[:4].tolist(), (got.double() - ref).abs().max().item())
+
+
+# tile, K splits, rows, K, columns: one row, ragged last row blocks, whole ones, a last
+# column tile of 64, and row counts that turn the grouped block order on (K = 128: multiples
+# of 64 row blocks, K = 1024: of 32 of the 128 tile)
+RESIDS = [(128, 1, 1, 128, 64), (128, 1, 257, 192, 576), (128, 2, 300, 256, 192), (128, 4, 300, 1024, 576), (128, 8, 65, 1024, 128),
+          (128, 1, 8192 - 37, 128, 256), (128, 1, 4096, 1024, 320), (256, 1, 257, 192, 256), (256, 1, 300, 128, 768),
+          (256, 1, 511, 448, 512), (256, 1, 16384 - 90, 128, 512), (0, 0, 8300, 256, 1024)]
+
+
+@pytest.mark.parametrize("tile,ks,M,K,rows", RESIDS)
+def test_residual(tile, ks, M, K, rows):
+    x, _, w, prods, mags = inputs(M, K, rows, 1, False, M + K)
+    y = torch.randn(M, rows, device="cuda")
+    ref = y.double() + prods[0]
+    run(RESID, tile, ks, K, rows, x, w, y=y)
+    close(y, ref, rel(K) * mags[0] + 2.0 ** -23 * ref.abs())
+
+
+@pytest.mark.parametrize("ks,M,rows", [(2, 65, 192), (4, 129, 1088)])
+def test_residual_with_next_norm(ks, M, rows):
+    """The kernel that adds the K parts also splits and norms the next product's rows."""
+    x, _, w, prods, mags = inputs(M, 512, rows, 1, False, M)
+    y = torch.randn(M, rows, device="cuda")
+    gain = 1 + 0.3 * torch.randn(rows, device="cuda")
+    nxt, rs = torch.empty(M, 2 * rows, dtype=torch.int16, device="cuda"), torch.empty(M, device="cuda")
+    ref = y.double() + prods[0]
+    run(RESID, 128, ks, 512, rows, x, w, y=y, next=nxt, next_gain=gain, next_rs=rs)
+    close(y, ref, rel(512) * mags[0] + 2.0 ** -23 * ref.abs())
+    hi, lo = joined(nxt, rows)
+    close(hi + lo, y.double() * gain.double(), 2.0 ** -16 * (y * gain).double().abs() + 1e-30)
+    inv = (y.double().pow(2).mean(1) + 1e-6).rsqrt()
+    close(rs, inv, inv * rows * 2.0 ** -23)
+
+
+@pytest.mark.parametrize("gain", [False, True])
+@pytest.mark.parametrize("tile,M,K,rows", [(128, 1, 128, 64), (128, 129, 192, 320), (128, 8192 - 5, 128, 128), (256, 257, 128, 128),
+                                           (256, 511, 320, 384), (256, 16384 - 90, 128, 256), (0, 8300, 256, 512)])
+def test_swiglu(tile, M, K, rows, gain):
+    x, t, w, (g, u), (sg, su) = inputs(M, K, rows, 2, gain, M + K)
+    ys = torch.empty(M, 2 * rows, dtype=torch.int16, device="cuda")
+    run(SWIGLU, tile, 1, K, rows, x, w, ys=ys, **t)
+    silu = g / (1 + torch.exp(-g))
+    hi, lo = joined(ys, rows)
+    bound = rel(K) * (1.1 * sg * (u.abs() + rel(K) * su) + silu.abs() * su) + (2.0 ** -16 + 2e-6) * (silu * u).abs() + 1e-30
+    close(hi + lo, silu * u, bound)
+
+
+@pytest.mark.parametrize("gain", [False, True])
+@pytest.mark.parametrize("tile,ks,M,K,rows,dh", [(128, 1, 1, 128, 64, 32), (128, 1, 140, 192, 576, 64), (128, 2, 257, 512, 192, 32),
+                                                 (128, 4, 300, 512, 576, 64), (128, 1, 8192 - 5, 128, 192, 64),
+                                                 (256, 1, 257, 128, 256, 32), (256, 1, 300, 192, 512, 64),
+                                                 (256, 1, 16384 - 90, 128, 256, 64), (0, 0, 8300, 128, 1024, 64)])
+def test_qkv(tile, ks, M, K, rows, dh, gain):
+    x, t, w, prods, mags = inputs(M, K, rows, 3, gain, M + K)
+    cap = M + 5
+    gen = torch.Generator().manual_seed(M)
+    pos = torch.randint(0, 50, (M,), generator=gen, dtype=torch.int32).cuda()
+    slot = torch.randperm(cap, generator=gen)[:M].int().cuda()
+    ang = torch.rand(50, dh // 2, generator=gen) * 6
+    rope = torch.stack([ang.cos(), ang.sin()], -1).cuda().contiguous()
+    q = torch.full((M, rows), 7.0, device="cuda")
+    kc, vc = (torch.full((rows // dh, cap, dh), 7.0, device="cuda") for _ in range(2))
+    run(QKV, tile, ks, K, rows, x, w, dh=dh, cap=cap, y=q, zero=torch.zeros(M, dtype=torch.int32, device="cuda"), pos=pos,
+        slot=slot, rope=rope, kc=kc, vc=vc, **t)
+    cs = rope.double()[pos.long()][:, None]  # [M, 1, dh / 2, 2]
+
+    def turned(p, s):
+        a, m = p.view(M, rows // dh, dh // 2, 2), s.view(M, rows // dh, dh // 2, 2).sum(-1, keepdim=True).expand(-1, -1, -1, 2)
+        r = torch.stack([a[..., 0] * cs[..., 0] - a[..., 1] * cs[..., 1], a[..., 0] * cs[..., 1] + a[..., 1] * cs[..., 0]], -1)
+        return r.view(M, rows), m.reshape(M, rows)
+
+    def cached(c):
+        return c[:, slot.long()].permute(1, 0, 2).reshape(M, rows)
+
+    for got, (ref, mag) in ((q, turned(prods[0], mags[0])), (cached(kc), turned(prods[1], mags[1])), (cached(vc), (prods[2], mags[2]))):
+        close(got, ref, rel(K) * mag + 1e-30)
+    other = torch.ones(cap, dtype=torch.bool)
+    other[slot.cpu().long()] = False
+    assert (kc[:, other.cuda()] == 7).all() and (vc[:, other.cuda()] == 7).all()
+
+
+@pytest.mark.parametrize("kind,tile,ks,M,K,rows", [(RESID, 256, 2, 300, 256, 256), (RESID, 256, 1, 300, 256, 320), (RESID, 128, 3, 65, 256, 64),
+                                                   (SWIGLU, 128, 2, 65, 256, 64), (RESID, 128, 1, 65, 96, 64), (RESID, 64, 1, 65, 128, 64)])
+def test_plans_that_no_kernel_takes_are_refused(kind, tile, ks, M, K, rows):
+    c = Product(kind=kind, tile=tile, ks=ks, M=M, N=rows * (2 if kind == SWIGLU else 1), K=K, rows=rows)
+    assert mbp.lib().mbp_check_product(ctypes.byref(c)) == 1

@@ -80,3 +80,24 @@ def test_decode_many_rows(batch, head):
         dec.accept(acc)
         for x, a in zip(xs, acc):
             x += a
+
+
+@pytest.mark.parametrize("batch,T,groups", [(64, 150, 1), (20, 200, 2)])
+def test_prefill_key_groups(batch, T, groups):
+    """Batches whose prefill attention runs its keys in one wave group, and in two, onto
+    split rows; prompts of unequal length leave ragged last row blocks in the products (the
+    larger batch's gate/up on the 256 x 256 tile)."""
+    lens = [T - b % 7 for b in range(batch)]
+    assert on_split_rows(D64, sum(lens))
+    blocks = sum((n + 63) // 64 for n in lens) * D64.n_heads
+    assert mbp.lib().mbp_check_prefill_groups(blocks, T, 0) == groups
+    raw = synth.make_weights(D64, seed=batch, gain_jitter=0.3)
+    W = oracle.to_float64(raw)
+    dec = new_decoder(D64, raw, batch, T + 20)
+    xs = [[int(v) for v in synth.make_prompt(b, n)] for b, n in enumerate(lens)]
+    dec.prefill(xs)
+    dec.decode_step(2, 0.75)
+    logits = dec.logits().double().cpu().numpy()
+    for b in (0, 1, 6, batch // 2, batch - 1):
+        err = np.max(np.abs(logits[b] - oracle.step_logits(W, D64, xs[b], 2)))
+        assert err <= TOL, f"row {b}: {err:.3g}"
