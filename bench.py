@@ -67,10 +67,11 @@ def cpu_threads():
 COPY_CAL_BYTES = 256 << 20
 # HBM traffic per launch of the dominant kernel class, from counter runs of this
 # command (profiles/<class>_<workload>_hbm_counters.md), valid only while the code of
-# the source the class is built from is the code that was measured.
+# every source the class's kernels are built from is the code that was measured.
 CSRC = os.path.join(ROOT, "paper_2608_15454_amd", "csrc")
-CLASS_SOURCE = {"engine": "engine.hip", "gemv": "kernels.hip", "gemm": "kernels.hip", "attention": "kernels.hip",
-                "other": "kernels.hip"}
+CLASS_SOURCES = {"engine": ("engine.hip", "dev.h"), "gemv": ("kernels.hip", "dev.h"),
+                 "gemm": ("kernels.hip", "planes.hip", "dev.h"), "attention": ("kernels.hip", "dev.h"),
+                 "other": ("kernels.hip", "planes.hip", "dev.h")}
 
 
 def traffic_key(workload, logit_gain=1.0):
@@ -92,20 +93,23 @@ def code_digest(path):
     return hashlib.sha256(src.encode()).hexdigest()
 
 
-def measured_traffic(kernel_class, workload):
+def digest_lines(kernel_class, csrc=CSRC):
+    """The lines of a counter record that name the code it was measured on."""
+    return [f"- {src} code sha256: `{code_digest(os.path.join(csrc, src))}`" for src in CLASS_SOURCES[kernel_class]]
+
+
+def measured_traffic(kernel_class, workload, profiles=os.path.join(ROOT, "profiles"), csrc=CSRC):
     """Bytes per launch recorded for kernel_class on workload, or None when there is no
-    record or the code of the class's source has changed since the counters were taken."""
-    path = os.path.join(ROOT, "profiles", f"{kernel_class}_{workload}_hbm_counters.md")
-    source = CLASS_SOURCE.get(kernel_class)
-    if source is None or not os.path.exists(path):
+    record or the code of one of the class's sources has changed since the counters were
+    taken."""
+    path = os.path.join(profiles, f"{kernel_class}_{workload}_hbm_counters.md")
+    if kernel_class not in CLASS_SOURCES or not os.path.exists(path):
         return None
-    fields = {}
-    for line in open(path):
-        if line.startswith("- ") and ": " in line:
-            k, v = line[2:].split(": ", 1)
-            fields[k.strip()] = v.strip().strip("`")
-    if fields.get(f"{source} code sha256") != code_digest(os.path.join(CSRC, source)) \
-            or fields.get("class") != kernel_class or fields.get("workload") != workload:
+    lines = [line.strip() for line in open(path) if line.startswith("- ")]
+    if not all(line in lines for line in digest_lines(kernel_class, csrc)):
+        return None
+    fields = dict(line[2:].split(": ", 1) for line in lines if ": " in line)
+    if fields.get("class") != kernel_class or fields.get("workload") != workload:
         return None
     return int(fields["hbm bytes per launch"])
 

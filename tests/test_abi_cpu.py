@@ -191,6 +191,22 @@ def test_counter_records_follow_code_not_comments(tmp_path):
             assert "code sha256: `" in open(os.path.join(ROOT, "profiles", rec)).read(), rec
 
 
+@pytest.mark.parametrize("cls,edited,valid", [("gemm", "planes.hip", False), ("gemm", "kernels.hip", False), ("gemm", "dev.h", False),
+                                              ("gemm", "engine.hip", True), ("engine", "engine.hip", False), ("engine", "planes.hip", True),
+                                              ("attention", "kernels.hip", False), ("attention", "planes.hip", True)])
+def test_counter_records_follow_every_source(tmp_path, cls, edited, valid):
+    """A record of a class counts while no source of that class's kernels has changed."""
+    import bench
+
+    for f in ("kernels.hip", "planes.hip", "engine.hip", "dev.h"):
+        (tmp_path / f).write_text(f"int f() {{ return {len(f)}; }}\n")
+    rec = [f"- class: {cls}", "- workload: w", "- hbm bytes per launch: 12"] + bench.digest_lines(cls, str(tmp_path))
+    (tmp_path / f"{cls}_w_hbm_counters.md").write_text("\n".join(rec) + "\n")
+    assert bench.measured_traffic(cls, "w", str(tmp_path), str(tmp_path)) == 12
+    (tmp_path / edited).write_text("int f() { return 0; }\n")
+    assert bench.measured_traffic(cls, "w", str(tmp_path), str(tmp_path)) == (12 if valid else None)
+
+
 def test_inline_asm_declares_m0():
     """An asm statement that writes m0 lists it as clobbered: the compiler keeps lane and
     LDS indices there and would read the asm's value."""
