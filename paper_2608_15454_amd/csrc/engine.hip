@@ -748,7 +748,8 @@ __device__ __forceinline__ AttnRow attn_row(const ECall& c, int i) {
 // each.  With one split per (row, head) (short contexts), the block takes all cached
 // keys on waves 1..EW-1 and this pass's keys on wave 0, and writes the output itself:
 // the partials' trip to the merge operation and its own step are saved.  The waves' (max, sum,
-// numerator) are combined in LDS and the block writes one partial.  r0: the rows of
+// numerator) are combined in LDS; with several splits the block writes one partial of them.
+// r0: the rows of
 // the block's first item (it = the block index), loaded once per launch.
 // Softmax exps are __expf (v_exp_f32 on x log2 e), as in the per-kernel attention.
 template <typename KV, int DH, class Late = NoHook>

@@ -8,7 +8,7 @@
 //   K >= 2048; 64 of float32): each weight byte is read from HBM once per launch with
 //   16-byte loads, issued before the activations are loaded;
 // - for more rows of bfloat16 weights, the row GEMM (17..64 rows) and MFMA tiles of
-//   64 x 64 (split-K); passes of 65 rows and more run on split rows (planes.hip).
+//   64 x 64 (split-K); long passes run on split rows (planes.hip; the line is planes_layer).
 // Decode attention splits the keys over blocks and merges the splits in a second
 // kernel; several rows of one sequence share each K/V tile (the multi-query kernel).
 // Prefill and the full-sequence forward use MFMA attention over 64-query tiles.
@@ -926,8 +926,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // float16 values, staged in LDS as [key][dim] and [dim][key].
 // MFMA operand layout: lane l supplies row / column l % 32 and the 8 k positions
 // 8 (l / 32) .. +7 of each 16-wide k step.  K tiles are loaded straight to LDS one block
-// ahead (no registers hold them).  Three waves per SIMD: 168 VGPRs and 8 bytes of scratch
-// (two waves per SIMD need no scratch and measure slower).
+// ahead (no registers hold them).  168 VGPRs, so three waves per SIMD; in four key groups,
+// whose grids leave most of the chip free anyway, 202 to 204 and two.
 
 template <int KG, bool SPLIT>
 __global__ __launch_bounds__(128 * KG, KG == 4 ? 2 : 3) void attn_prefill_mfma_kernel(Attn a, const int32_t* tiles) {
