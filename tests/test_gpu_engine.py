@@ -124,11 +124,24 @@ def test_engine_matches_per_kernel_path_d1024():
     assert np.array_equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("batch,length", [(1, 222), (2, 445)])
+def test_engine_attention_splits_edge(batch, length):
+    """Short contexts run a (row, head)'s attention in one block, longer ones in split
+    keys with a merge: steps across 224 cached float32 keys for one row, and across 448 for
+    several, for the encoder and NT decoder; the LM module and MB window stay below."""
+    raw = synth.make_weights(synth.SMALL_F32, seed=5, gain_jitter=0.2, logit_gain=10.0)
+    W = oracle.to_float64(raw)
+    dec = new_decoder(synth.SMALL_F32, raw, batch, 1000)
+    prompts = [synth.make_prompt(20 + b, length - 3 * b) for b in range(batch)]
+    st = forced_run(dec, W, synth.SMALL_F32, prompts, 5, 3, 0.75, tol=base_tol(synth.SMALL_F32) * 10, timing=True)
+    assert st.timing["engine"][0] > 0
+
+
 # the last encoder pass below the line between one block per (row, head) and split keys,
 # for float32 keys (224, and 448 from four rows on) and float16 ones (448 and 896)
 @pytest.mark.parametrize("model,batch,length", [(SMALL, 1, 222), (SMALL, 2, 221), (SMALL, 4, 445), (D1024, 1, 446),
                                                 (D1024, 3, 445), (D1024, 4, 893)])
-def test_engine_attention_splits_edge(model, batch, length):
+def test_engine_attention_line(model, batch, length):
     """Steps that cross the line at which a (row, head)'s attention goes from one block to
     split keys with a merge, for the encoder and NT decoder; the LM module and MB window
     stay below it."""

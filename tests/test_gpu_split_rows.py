@@ -11,7 +11,7 @@ import torch  # noqa: F401  (before the library is loaded: both use torch's HIP 
 import oracle
 import paper_2608_15454_amd as mbp
 import synth
-from gpu_harness import new_decoder
+from gpu_harness import forced_run, new_decoder
 from test_gpu_forward import check
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +101,35 @@ def test_prefill_key_groups(batch, T, groups):
     for b in (0, 1, 6, batch // 2, batch - 1):
         err = np.max(np.abs(logits[b] - oracle.step_logits(W, D64, xs[b], 2)))
         assert err <= TOL, f"row {b}: {err:.3g}"
+
+
+# small models: passes of 65 rows and more below the line of the rule
+D256 = synth.SMALL_F32.replace(dtype="bf16")
+D128 = synth.ModelConfig(d_model=128, n_heads=4, n_enc=1, n_lm=1, n_nb=1, n_mb=1, head="lca", dtype="bf16")
+
+
+@pytest.mark.parametrize("model,T", [(D256, 64), (D256, 65), (D256, 127), (D256, 128), (D256, 129), (D256, 257),
+                                     (D256, 700), (D128, 65), (D128, 200)])
+def test_forward_row_edges_small(model, T):
+    assert not on_split_rows(model, T)
+    raw = synth.make_weights(model, seed=T, gain_jitter=0.3)
+    dec = new_decoder(model, raw, 1, T + 8)
+    check(dec, oracle.to_float64(raw), model, synth.make_prompt(T, T), TOL)
+
+
+@pytest.mark.parametrize("kw", [dict(engine=False), dict(kv_dtype=0), dict(kv_dtype=1), dict(max_chunk=100)])
+def test_forward_cache_types_small(kw):
+    raw = synth.make_weights(D256, seed=2, gain_jitter=0.3)
+    T = 333 if "max_chunk" in kw else 150
+    dec = new_decoder(D256, raw, 1, T + 50, **kw)
+    check(dec, oracle.to_float64(raw), D256, synth.make_prompt(2, T), TOL * (8 if kw.get("kv_dtype") == 1 else 1))
+
+
+@pytest.mark.parametrize("batch,head", [(65, "lca"), (70, "lca"), (66, "mlp")])
+def test_decode_many_rows_small(batch, head):
+    model = D256.replace(head=head, n_mb=2)
+    raw = synth.make_weights(model, seed=batch, gain_jitter=0.3)
+    W = oracle.to_float64(raw)
+    dec = new_decoder(model, raw, batch, 330)
+    prompts = [synth.make_prompt(b, 300 if b == 3 else 6 + b % 9) for b in range(batch)]
+    forced_run(dec, W, model, prompts, 2, 3, 0.75, tol=TOL, label=f"{head} {batch}")
