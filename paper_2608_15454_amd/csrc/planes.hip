@@ -509,7 +509,8 @@ bool planes_fit(int M, int N, int K, int n_mat) {
 PlanesPlan planes_plan(const PlaneLinear& P) {
   const int64_t t128 = (int64_t)column_blocks(P, 128) * ((P.M + 127) / 128);
   const int nmat = P.mats.mode == MAT_QKV ? P.mats.rows : P.N;
-  if (P.N % 256 == 0 && nmat % 256 == 0) {
+  // gate/up of K > 4096 keeps the 128 tile, whose silu is the nearer one
+  if (P.N % 256 == 0 && nmat % 256 == 0 && !(P.kind == EPI_SWIGLU && P.K > 4096)) {
     const int64_t t256 = (int64_t)(P.N / 256) * ((P.M + 255) / 256);
     const int64_t rem = t128 % 512;
     if (100 * ((t256 + 255) / 256) <= 54 * (t128 / 512) + (rem == 0 ? 0 : rem <= 256 ? 40 : 54)) return {256, 1};
