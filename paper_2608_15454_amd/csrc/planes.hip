@@ -44,7 +44,7 @@ constexpr int kPlanesMinRows = 65;
 //
 // Bound by the matrix cores, at the clock their power leaves: two MFMAs per product keep
 // them busy 65 % of the cycles (SQ_VALU_MFMA_BUSY_CYCLES over the 256 tile's launches in
-// prompts of 131072 rows) at 1.76 GHz.  Against a
+// prompts of 131072 rows) at 1.72 GHz.  Against a
 // tile that read float32 rows, split them in every block and staged them through
 // registers (44-48 % busy), at M = 131072, d = 1024: gate/up 4093 -> 3366 us (653
 // TFLOP/s), down 2072 -> 1658 (663), output 669 -> 591, QKV 2181 -> 1730; at M = 32768,
